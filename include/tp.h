@@ -102,9 +102,10 @@ tp_status tp_plan_create(const tp_geometry* g, tp_plan** out);
  * them; the caller must ensure no enqueued work still uses them. */
 tp_status tp_plan_destroy(tp_plan* plan);
 
-/* Tuning of the backprojection kernel for one storage type of its input
- * (results are bitwise identical for every legal choice: each slice always
- * sums its angles in order).
+/* Tuning of tp_backproject for one storage type of its input (results are
+ * bitwise identical for every legal choice: each slice always sums its angles
+ * in order).  tp_fbp_chunk keeps its filtered rows in blocks of 8 slices and
+ * picks its own tiles.
  *   slices_per_block in {1, 2, 4, 8, 16}: slices sharing one coordinate evaluation;
  *   angles_per_block in {8, 16, 32, 64}: angles staged in LDS per step;
  *   the staged block, angles x 48 bins x pitch (slices x 4 bytes, 2 for F16,
@@ -127,8 +128,8 @@ tp_status tp_filter_prepare(int32_t pad_len, tp_filter_kind kind);
  * storage type, built before the first chunk (FFT plans created once and
  * executed per chunk, paper Section 2.2; the filter and 16-bit storage
  * choices of Section 2.4): the window's tables at the plan's pad length and
- * the dynamic-LDS limit of the backprojection kernel that the plan's current
- * tiling for `storage` selects.  After it, tp_fbp_chunk and tp_backproject
+ * the dynamic-LDS limits of tp_fbp_chunk's backprojection kernels and of the
+ * one that the plan's current tiling for `storage` selects.  After it, tp_fbp_chunk and tp_backproject
  * with that (kind, storage) allocate nothing and make no one-time runtime
  * call, so they may be graph-captured.  Call it again after
  * tp_plan_set_tuning.  The plan's device must be current.  Errors: TP_EINVAL
@@ -272,7 +273,7 @@ tp_status tp_radon(const tp_plan* plan, const float* vol, int32_t n_rows, float*
  *   vol = (pi / n_angles) R^T ( H * normalize(proj, dark, flat) )
  * The -log sinogram never leaves the chip: the filter kernel normalises raw
  * counts in registers, filters in FP32 and stores only the filtered rows, in
- * `storage` precision, into the workspace.  Inputs as for tp_normalize
+ * `storage` precision and in whole blocks of 8 slices, into the workspace.  Inputs as for tp_normalize
  * (n_angles, n_det from the plan); vol: dev float [n_rows][N][N] (overwritten).
  * kind: filter window at the plan's pad length 2^ceil(log2(2 n_det)); windows
  * other than TP_RAMP build their tables on first use (tp_filter_prepare first

@@ -18,6 +18,7 @@
 // filtered rows (storage precision); the -log sinogram never reaches HBM.
 // Sign flips are written as 0 - x: the fneg form of a half-precision store
 // trips an instruction-selection failure when packed FP32 is disabled.
+#include "blocked_rows.h"
 #include "fft_device.h"
 
 namespace tp {
@@ -66,16 +67,37 @@ k_filter(const TI* in, TO* out, int64_t n_lines, int n, int off, FilterTables ft
     }
 }
 
+// Where slice r's rows of angle a start in the blocked layout.
+template <int ST> __device__ __forceinline__ uint16_t* blocked_row(uint16_t* out, int r, int a, int na, int n) {
+    return out + 8 * ((static_cast<int64_t>(r >> 3) * na + a) * (Blocked<ST>::PB * static_cast<int64_t>(n))) + (r & 7);
+}
+
+// Work-group -> (slice r, piece of its angles): work-groups go to the 8 XCDs in
+// turn, and the 8 slices of a block run back to back on one XCD for the same
+// piece, so their 2-byte stores of a line meet in that XCD's L2.
+__device__ __forceinline__ void blocked_work(int n_rows, int pieces, int& r, int& piece) {
+    const int id = blockIdx.x, xcd = id & 7, s = id >> 3, high = min(n_rows, 8);
+    const int item = s / high * 8 + xcd;
+    piece = item % pieces;
+    r = item / pieces * 8 + s % high;
+}
+unsigned blocked_grid(int n_rows, int pieces) {
+    const int64_t items = static_cast<int64_t>((n_rows + 7) / 8) * pieces;
+    return static_cast<unsigned>((items + 7) / 8 * 8 * (n_rows < 8 ? n_rows : 8));
+}
+
 // Rows (r, a) and (r, a + 1) of the chunk, a even; raw counts normalised in registers.
-template <typename TO>
+template <int ST>
 __global__ void __launch_bounds__(1024)
 k_norm_filter(RawInput in, const float* __restrict__ dmean, const float* __restrict__ den, int n_angles,
-              int n, int off, FilterTables ft, TO* out) {
+              int n_rows, int n, int off, FilterTables ft, uint16_t* out) {
     extern __shared__ float2 buf[];
     const int tid = threadIdx.x, B = blockDim.x;
     const int pairs = (n_angles + 1) >> 1;
-    const int r = blockIdx.x / pairs;
-    const int a0 = 2 * (blockIdx.x - r * pairs);
+    int r, pair;
+    blocked_work(n_rows, pairs, r, pair);
+    if (r >= n_rows) return;  // whole work-group
+    const int a0 = 2 * pair;
     const bool has1 = a0 + 1 < n_angles;
     const uint16_t* p0 = in.proj + a0 * in.proj_stride + static_cast<int64_t>(r) * n;
     const uint16_t* p1 = p0 + in.proj_stride;
@@ -89,12 +111,12 @@ k_norm_filter(RawInput in, const float* __restrict__ dmean, const float* __restr
     }
     __syncthreads();
     filter_in_lds(buf, n, off, ft);
-    TO* o0 = out + (static_cast<int64_t>(r) * n_angles + a0) * n;
-    TO* o1 = o0 + n;
+    uint16_t* o0 = blocked_row<ST>(out, r, a0, n_angles, n);
+    uint16_t* o1 = o0 + 8 * Blocked<ST>::PB * static_cast<int64_t>(n);
     for (int j = tid; j < n; j += B) {
         const float2 y = buf[off + j];
-        store_from_float(o0, j, y.x);
-        if (has1) store_from_float(o1, j, 0.0f - y.y);
+        store_blocked<ST>(o0, n, j, y.x);
+        if (has1) store_blocked<ST>(o1, n, j, 0.0f - y.y);
     }
 }
 
@@ -157,16 +179,18 @@ constexpr int kPairsPerGroup = 8;
 // and 12-15 right padding at compile time: padding slots load nothing and
 // hold no registers.  Otherwise the same tests run on the runtime offsets
 // (each is uniform over the work-group).
-template <int L, typename TO, bool HALF>
+template <int L, int ST, bool HALF>
 __global__ void __launch_bounds__(L / kRegPts)
-k_norm_filter_reg(RawInput in, const float* __restrict__ dmean, const float* __restrict__ rden, int n_angles, int n,
-                  int off, FilterTables ft, TO* out) {
+k_norm_filter_reg(RawInput in, const float* __restrict__ dmean, const float* __restrict__ rden, int n_angles, int n_rows,
+                  int n, int off, FilterTables ft, uint16_t* out) {
     extern __shared__ float2 lds[];
     constexpr int B = L / kRegPts;
     const int pairs = (n_angles + 1) >> 1;
     const int groups = (pairs + kPairsPerGroup - 1) / kPairsPerGroup;
-    const int r = blockIdx.x / groups;
-    const int g0 = (blockIdx.x - r * groups) * kPairsPerGroup;
+    int r, g0;
+    blocked_work(n_rows, groups, r, g0);
+    if (r >= n_rows) return;  // whole work-group
+    g0 *= kPairsPerGroup;
     const int g1 = min(pairs, g0 + kPairsPerGroup);
     const float* dm = dmean + static_cast<int64_t>(r) * n;
     const float* dn = rden + static_cast<int64_t>(r) * n;
@@ -235,15 +259,15 @@ k_norm_filter_reg(RawInput in, const float* __restrict__ dmean, const float* __r
             x[s] = make_float2(x[s].x * h, 0.0f - x[s].y * h);
         }
         reg_fft_w<L>(x, lds, w, t);
-        TO* o0 = out + (static_cast<int64_t>(r) * n_angles + a0) * n;
-        TO* o1 = o0 + n;
+        uint16_t* o0 = blocked_row<ST>(out, r, a0, n_angles, n);
+        uint16_t* o1 = o0 + 8 * Blocked<ST>::PB * static_cast<int64_t>(n);
 #pragma unroll
         for (int s = 0; s < kRegPts; ++s) {
             if (HALF && (s < 4 || s >= 12)) continue;
             const int j = t + B * s - off;
             if (HALF || (j >= 0 && j < n)) {
-                store_from_float(o0, j, x[s].x);
-                if (has1) store_from_float(o1, j, 0.0f - x[s].y);
+                store_blocked<ST>(o0, n, j, x[s].x);
+                if (has1) store_blocked<ST>(o1, n, j, 0.0f - x[s].y);
             }
         }
 #pragma unroll
@@ -316,30 +340,28 @@ hipError_t launch_filter_in(const void* in, tp_dtype out_dt, void* out, int64_t 
     return hipErrorInvalidValue;
 }
 
-template <typename TO>
+template <int ST>
 hipError_t launch_norm_filter_t(const RawInput& in, const float* dmean, const float* den, int n_angles,
                                 int n_rows, int n, const FilterTables& ft, void* out, hipStream_t st) {
     const int off = (ft.L - n) / 2;
-    const int64_t blocks = static_cast<int64_t>(n_rows) * ((n_angles + 1) / 2);
-    const dim3 grid(static_cast<unsigned>(blocks));
-    const int64_t reg_blocks =
-        static_cast<int64_t>(n_rows) * ((((n_angles + 1) / 2) + kPairsPerGroup - 1) / kPairsPerGroup);
-    const dim3 reg_grid(static_cast<unsigned>(reg_blocks));
-    TO* pout = static_cast<TO*>(out);
+    const int pairs = (n_angles + 1) / 2;
+    const dim3 grid(blocked_grid(n_rows, pairs));
+    const dim3 reg_grid(blocked_grid(n_rows, (pairs + kPairsPerGroup - 1) / kPairsPerGroup));
+    uint16_t* pout = static_cast<uint16_t*>(out);
     size_t lds = 0;
     hipError_t e = hipSuccess;
 #define TP_REG_CASE(LL)                                                                                    \
     case LL:                                                                                              \
         if (2 * n == LL) {                                                                                \
-            e = launch_reg<LL>(k_norm_filter_reg<LL, TO, true>, reg_grid, st, lds);                       \
+            e = launch_reg<LL>(k_norm_filter_reg<LL, ST, true>, reg_grid, st, lds);                       \
             if (e != hipSuccess) return e;                                                                \
-            hipLaunchKernelGGL((k_norm_filter_reg<LL, TO, true>), reg_grid, dim3(LL / kRegPts), lds, st, in, \
-                               dmean, den, n_angles, n, off, ft, pout);                                   \
+            hipLaunchKernelGGL((k_norm_filter_reg<LL, ST, true>), reg_grid, dim3(LL / kRegPts), lds, st, in, \
+                               dmean, den, n_angles, n_rows, n, off, ft, pout);                           \
         } else {                                                                                          \
-            e = launch_reg<LL>(k_norm_filter_reg<LL, TO, false>, reg_grid, st, lds);                      \
+            e = launch_reg<LL>(k_norm_filter_reg<LL, ST, false>, reg_grid, st, lds);                      \
             if (e != hipSuccess) return e;                                                                \
-            hipLaunchKernelGGL((k_norm_filter_reg<LL, TO, false>), reg_grid, dim3(LL / kRegPts), lds, st, in, \
-                               dmean, den, n_angles, n, off, ft, pout);                                   \
+            hipLaunchKernelGGL((k_norm_filter_reg<LL, ST, false>), reg_grid, dim3(LL / kRegPts), lds, st, in, \
+                               dmean, den, n_angles, n_rows, n, off, ft, pout);                           \
         }                                                                                                 \
         return hipGetLastError();
     switch (ft.L) {
@@ -351,10 +373,10 @@ hipError_t launch_norm_filter_t(const RawInput& in, const float* dmean, const fl
     }
 #undef TP_REG_CASE
     lds = static_cast<size_t>(ft.L) * sizeof(float2);
-    e = ensure_lds(k_norm_filter<TO>, lds);
+    e = ensure_lds(k_norm_filter<ST>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_norm_filter<TO>), grid, dim3(filter_block(ft.L)), lds, st, in, dmean, den, n_angles, n,
-                       off, ft, pout);
+    hipLaunchKernelGGL((k_norm_filter<ST>), grid, dim3(filter_block(ft.L)), lds, st, in, dmean, den, n_angles,
+                       n_rows, n, off, ft, pout);
     return hipGetLastError();
 }
 
@@ -374,10 +396,10 @@ hipError_t launch_norm_filter(const RawInput& in, const float* dmean, const floa
                               int n_rows, int n_det, const FilterTables& ft, tp_dtype out_dt, void* out,
                               hipStream_t st) {
     switch (out_dt) {
-        case TP_F32: return launch_norm_filter_t<float>(in, dmean, den, n_angles, n_rows, n_det, ft, out, st);
-        case TP_F16: return launch_norm_filter_t<__half>(in, dmean, den, n_angles, n_rows, n_det, ft, out, st);
+        case TP_F32: return launch_norm_filter_t<kStF32>(in, dmean, den, n_angles, n_rows, n_det, ft, out, st);
+        case TP_F16: return launch_norm_filter_t<kStF16>(in, dmean, den, n_angles, n_rows, n_det, ft, out, st);
         case TP_BF16:
-            return launch_norm_filter_t<uint16_t>(in, dmean, den, n_angles, n_rows, n_det, ft, out, st);
+            return launch_norm_filter_t<kStBF16>(in, dmean, den, n_angles, n_rows, n_det, ft, out, st);
     }
     return hipErrorInvalidValue;
 }

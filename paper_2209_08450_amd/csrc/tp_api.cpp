@@ -991,6 +991,10 @@ tp_status tp_prepare(const tp_plan* plan, tp_filter_kind kind, tp_dtype storage)
     tp_status s = filter_tables(plan->filt.L, kind, &ft, nullptr);
     if (s != TP_OK) return s;
     e = tp::prepare_backproject(storage, plan->bp_k[storage], plan->bp_a[storage]);
+    if (e == hipSuccess)
+        e = tp::launch_backproject_blocked(plan->geo, nullptr, storage, 0, 0.0f, nullptr, TP_F32, nullptr);
+    if (e == hipSuccess && storage == TP_F16)
+        e = tp::launch_backproject_blocked(plan->geo, nullptr, storage, 0, 0.0f, nullptr, TP_F16, nullptr);
     if (e != hipSuccess) return hip_fail(e, "backprojection kernel attribute");
     return TP_OK;
 }
@@ -1210,7 +1214,7 @@ tp_status tp_radon(const tp_plan* plan, const float* vol, int32_t n_rows, float*
 size_t tp_fbp_workspace_bytes(const tp_plan* plan, int32_t n_rows, tp_dtype storage) {
     if (!plan || n_rows <= 0 || !valid_dtype(storage)) return 0;
     return tp_normalize_workspace_bytes(n_rows, plan->n) +
-           align256(static_cast<size_t>(n_rows) * plan->na * plan->n * dtype_size(storage));
+           align256(tp::blocked_rows_bytes(n_rows, plan->na, plan->n, storage));
 }
 
 tp_status tp_fbp_chunk(const tp_plan* plan, const uint16_t* proj, int64_t proj_stride, const uint16_t* dark,
@@ -1247,9 +1251,6 @@ tp_status tp_fbp_chunk_out(const tp_plan* plan, const uint16_t* proj, int64_t pr
     if (reinterpret_cast<uintptr_t>(workspace) & 255) return fail(TP_EINVAL, "workspace not 256-byte aligned");
     const size_t need = tp_fbp_workspace_bytes(plan, n_rows, storage);
     if (workspace_bytes < need) return fail(TP_EINVAL, "workspace %zu < %zu bytes", workspace_bytes, need);
-    const int K = plan->bp_k[storage], A = plan->bp_a[storage];
-    if ((n_rows + K - 1) / K > 65535)
-        return fail(TP_EINVAL, "n_rows=%d too large for slices_per_block=%d", n_rows, K);
     if (static_cast<int64_t>(n_rows) * ((plan->na + 1) / 2) > 0x7fffffffLL)
         return fail(TP_EINVAL, "n_rows=%d x n_angles=%d too large for one call", n_rows, plan->na);
     auto st = static_cast<hipStream_t>(stream);
@@ -1272,8 +1273,8 @@ tp_status tp_fbp_chunk_out(const tp_plan* plan, const uint16_t* proj, int64_t pr
     e = tp::launch_norm_filter(in, dmean, den, plan->na, n_rows, plan->n, ft, storage, filt, st);
     if (e != hipSuccess) return hip_fail(e, "norm_filter launch");
     if ((e = mark(2)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-    e = tp::launch_backproject(plan->geo, filt, storage, n_rows, static_cast<float>(M_PI / plan->na), vol, vol_dtype,
-                               0, K, A, st);
+    e = tp::launch_backproject_blocked(plan->geo, filt, storage, n_rows, static_cast<float>(M_PI / plan->na), vol,
+                                       vol_dtype, st);
     if (e != hipSuccess) return hip_fail(e, "backproject launch");
     if ((e = mark(3)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     return TP_OK;
