@@ -51,18 +51,10 @@
 #include <type_traits>
 
 #include "blocked_rows.h"
+#include "mfma_lds.h"
 
 namespace tp {
 namespace {
-
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef float f2_t __attribute__((ext_vector_type(2)));
-typedef float f4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
-typedef short s4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s4_t* lds_s4_t;
 
 template <int TB, int NT> struct Tile {
     static constexpr int kBlocks = TB / 4;             // 4x4 blocks per side
@@ -74,20 +66,13 @@ template <int TB, int NT> struct Tile {
     static constexpr int kBytes = 64 * kWinB;          // of a tile of 16 slices for two angles
 };
 
-// LDS layout of 16-bit samples: [plane][angle pair][16-slice tile][bin][angle of the pair][slice].
-// Four consecutive bins of one angle lie in four different 64-byte quarters of
-// a 256-byte line, in the half of each that belongs to the angle: a read of 4
-// bins x 16 slices for two angles (32 lanes, 256 bytes) meets every bank once
-// wherever the two windows start.
+// LDS layout: [plane][angle pair][16-slice tile][bin][angle of the pair][slice] (mfma_lds.h).
 constexpr int kRing = 4;
 template <int ST, int TB, int NT>
 constexpr size_t bb_lds() {
     return size_t{2} * Blocked<ST>::PB * (Blocked<ST>::A / 2) * NT * Tile<TB, NT>::kBytes + kRing * Blocked<ST>::A * 24 +
            7 * 16;
 }
-
-// What samples off the detector and past the last angle are read from.
-__device__ __align__(16) uint32_t g_zero[4];
 
 // Tile of work-group `wg` among nb x nb tiles.  Work-groups are dispatched
 // round-robin over the 8 XCDs, so wg % 8 names the XCD; each XCD gets one
@@ -135,27 +120,9 @@ __device__ __forceinline__ u4_t place_pair(uint32_t p, u4_t sel) {
 }
 
 
-// 8 bins of 16 slices from p (bytes of the lane's row and slices), transposed:
-// lane l of each 16 gets slice l's samples.
-__device__ __forceinline__ u4_t read_bins(const unsigned char* p) {
-    struct { s4_t lo, hi; } v;
-    v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_t)(p));
-    v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4_t)(p + 256));  // 4 bins on
-    return __builtin_bit_cast(u4_t, v);
-}
-
-// 16 bytes per lane from the lane's global address to LDS bytes lds .. lds +
-// 1023, in lane order.  No register receives the data, so nothing waits for it
-// but wait_loads(): for the builtin the compiler waits before the next LDS read
-// of any kind, which ends the overlap with the products.
-__device__ __forceinline__ void load_lds16(const void* p, uint32_t lds) {
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(p), "{m0}"(lds) : "memory");
-}
-__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-template <int ST, typename OutT, int TB, int NT>
 // 32-voxel tiles are held to 128 registers, 4 waves per SIMD: two work-groups
 // of 8 waves per CU, or one of 16.
+template <int ST, typename OutT, int TB, int NT>
 __global__ void __launch_bounds__((Tile<TB, NT>::kThreads)) __attribute__((amdgpu_waves_per_eu(TB == 32 ? 4 : 1)))
 k_backproject_blocked(GeoTables g, const uint16_t* __restrict__ rows, int n_rows, float scale,
                       OutT* __restrict__ vol) {
@@ -233,8 +200,7 @@ k_backproject_blocked(GeoTables g, const uint16_t* __restrict__ rows, int n_rows
     const int lpar = (lane >> 1) & 1;
     const int last8 = (n_rows - 1) >> 3;
     const int64_t slab = static_cast<int64_t>(na) * PB * n;  // 16-byte units of 8 slices' rows
-    const uint32_t lds0 = static_cast<uint32_t>(
-        reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char*)(smem)));
+    const uint32_t lds0 = lds_address(smem);
     const u4_t* units = reinterpret_cast<const u4_t*>(rows);
     const int64_t odd = (lane & 1) ? slab : 0;                // the tile's second 8 slices
     const u4_t* lane_units = units + static_cast<int64_t>(lpar * PB) * n;
@@ -303,17 +269,12 @@ k_backproject_blocked(GeoTables g, const uint16_t* __restrict__ rows, int n_rows
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
 #pragma unroll
-                    for (int b = 0; b < PB; ++b) o.q[t][b] = read_bins(src + b * kPlane + t * kTile);
+                    for (int b = 0; b < PB; ++b) o.q[t][b] = read_slots(src + b * kPlane + t * kTile);
                 const float w = coord_frac(s), omw = 1.0f - w;
                 if constexpr (PA == 1) {
                     o.p[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2_t{omw, w}), half2_t));
                 } else {
-                    const half2_t hi = __builtin_convertvector((f2_t{omw, w}), half2_t);
-                    // what the rounded weights miss (one mixed-precision FMA each)
-                    const f2_t lo{__builtin_fmaf(static_cast<float>(hi.x), -1.0f, omw),
-                                  __builtin_fmaf(static_cast<float>(hi.y), -1.0f, w)};
-                    o.p[0] = __builtin_bit_cast(uint32_t, hi);
-                    o.p[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, half2_t));
+                    split_pair(omw, w, o.p[0], o.p[1]);
                 }
             };
             auto add = [&](int i, const Block& o) {
@@ -332,9 +293,7 @@ k_backproject_blocked(GeoTables g, const uint16_t* __restrict__ rows, int n_rows
 #pragma unroll
                         for (int b = PB - 1; b >= 0; --b) {
                             if (c + b > 1) continue;
-                            sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, wt[c]),
-                                                                         __builtin_bit_cast(half8_t, o.q[t][b]), sum, 0,
-                                                                         0, 0);
+                            sum = mfma16(wt[c], o.q[t][b], sum);
                         }
                     acc[i][t] = ST == kStF32 ? acc[i][t] + sum : sum;
                 }

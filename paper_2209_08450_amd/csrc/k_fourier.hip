@@ -25,22 +25,19 @@
 //                 store the L + 1 signed-frequency samples of the angle;
 //   k_fr_grid     for every grid point, sum the Gaussian-weighted samples of
 //                 every angle whose ray passes within the truncation radius
-//                 (a gather: no atomics, a fixed summation order; FP64
-//                 accumulation over batches of 16 angles);
+//                 (a gather on the matrix cores: no atomics, a fixed
+//                 summation order);
 //   k_fr_rows     inverse FFT along the grid's fast axis, keeping the N
 //                 output rows, stored in 16-wide column groups;
 //   k_fr_cols     inverse FFT along the other axis, deconvolution, split of
 //                 the two slices, store.
+#include <type_traits>
+
 #include "fft_device.h"
+#include "mfma_lds.h"
 
 namespace tp {
 namespace {
-
-constexpr float kPiF = 3.14159265358979323846f;
-constexpr int kFrTile = 16;             // grid points per tile side (4 waves of 8x8)
-constexpr int kFrBatch = 16;            // angles staged per batch
-constexpr float kFrHalfDiag = 10.6066017f;   // 7.5 sqrt(2): tile centre to its farthest point
-constexpr float kFrWaveHalfDiag = 4.9497475f;  // 3.5 sqrt(2): the same for a wave's 8x8 block
 
 __device__ __forceinline__ float2 cconj(float2 a) { return make_float2(a.x, 0.0f - a.y); }
 
@@ -52,6 +49,11 @@ __device__ __forceinline__ void fr_store(float* p, int64_t i, float v) { p[i] = 
 __device__ __forceinline__ void fr_store(__half* p, int64_t i, float v) {
     asm volatile("" : "+v"(v));
     p[i] = __float2half_rn(v);
+}
+
+// A value all lanes agree on, in a scalar register.
+__device__ __forceinline__ float uniform(float v) {
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
 int fr_block(int L) {
@@ -69,16 +71,50 @@ hipError_t fr_lds(K kernel, size_t bytes) {
 }
 
 // ---------------------------------------------------------------------------
+// Spectra rows: groups of four pairs of slices side by side, so that one
+// 16-byte piece holds a sample of four pairs, in two FP16 planes; entry 0 of a
+// row is zero (what the gather reads off either end), frequency k is entry
+// k + L/2 + 1.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t* spectra_row(uint32_t* spec, int p, int slot, const FourierTables& t) {
+    return spec + ((static_cast<int64_t>(p / kFrPairGroup) * t.na + slot) * 2 * t.SL) * kFrPairGroup + p % kFrPairGroup;
+}
+__device__ __forceinline__ void spectra_store(uint32_t* row, int k, int SL, float2 v) {
+    uint32_t hi, lo;
+    split_pair(v.x, v.y, hi, lo);
+    row[static_cast<int64_t>(k) * kFrPairGroup] = hi;
+    row[(static_cast<int64_t>(SL) + k) * kFrPairGroup] = lo;
+}
+__device__ __forceinline__ void spectra_zero(uint32_t* row, int SL) {
+    row[0] = 0;
+    row[static_cast<int64_t>(SL) * kFrPairGroup] = 0;
+}
+// Work-group -> (pair, piece of the angles): work-groups go to the 8 XCDs in
+// turn, and the four pairs of a group run back to back on one XCD for the same
+// piece, so their 4-byte stores of a line meet in that XCD's L2.
+__device__ __forceinline__ void spectra_work(int pairs, int pieces, int& p, int& piece) {
+    const int id = blockIdx.x, xcd = id & 7, s = id >> 3, high = min(pairs, kFrPairGroup);
+    const int item = s / high * 8 + xcd;
+    piece = item % pieces;
+    p = item / pieces * kFrPairGroup + s % high;
+}
+unsigned spectra_grid(int pairs, int pieces) {
+    const int64_t items = static_cast<int64_t>((pairs + kFrPairGroup - 1) / kFrPairGroup) * pieces;
+    return static_cast<unsigned>((items + 7) / 8 * 8 * (pairs < kFrPairGroup ? pairs : kFrPairGroup));
+}
+
+// ---------------------------------------------------------------------------
 // Spectra: one work-group per (pair of slices, angle).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(1024)
 k_fr_spectra(RawInput in, int rows, const float* __restrict__ dmean, const float* __restrict__ rden,
-             const float2* __restrict__ tw, FourierTables t, float2* __restrict__ spec) {
+             const float2* __restrict__ tw, FourierTables t, uint32_t* __restrict__ spec) {
     extern __shared__ float2 buf[];
     const int tid = threadIdx.x, B = blockDim.x;
     const int L = t.L, n = t.n, off = (L - n) / 2, h = L / 2;
-    const int p = blockIdx.x / t.na;
-    const int a = blockIdx.x - p * t.na;
+    int p, a;
+    spectra_work((rows + 1) / 2, t.na, p, a);
+    if (2 * p >= rows) return;  // whole work-group
     const int z0 = 2 * p;
     const bool has1 = z0 + 1 < rows;
     const uint16_t* p0 = in.proj + a * in.proj_stride + static_cast<int64_t>(z0) * n;
@@ -98,177 +134,315 @@ k_fr_spectra(RawInput in, int rows, const float* __restrict__ dmean, const float
     fft_forward_lds(buf, L, t.log2L, tw);
     const int sl = t.slot[a];
     const bool rev = (sl & 1) != 0;
-    float2* row = spec + (static_cast<int64_t>(p) * t.na + (sl >> 1)) * t.SL;
+    uint32_t* row = spectra_row(spec, p, sl >> 1, t);
+    if (tid == 0) spectra_zero(row, t.SL);
     for (int m = tid; m < L; m += B) {
         const float2 X = buf[m];
         const int k = m < h ? m : m - L;  // m = L/2 is the -L/2 term
-        row[(rev ? -k : k) + h] = cmul(X, t.E[k + h]);
-        if (m == h) row[(rev ? -h : h) + h] = cmul(X, t.E[L]);  // and its +L/2 copy
+        spectra_store(row, (rev ? -k : k) + h + 1, t.SL, cmul(X, t.E[k + h]));
+        if (m == h) spectra_store(row, (rev ? -h : h) + h + 1, t.SL, cmul(X, t.E[L]));  // and its +L/2 copy
     }
 }
 
 // ---------------------------------------------------------------------------
 // Gather onto the Cartesian frequency grid.
 //
-// Work-group: one 16x16 tile of one pair's grid, 4 waves of 8x8 points.  The
-// grid is periodic (M points per side), so tiles near its edge also gather
-// through their images shifted by +-M.  For each tile image only the angles
-// whose ray passes within (radius + half-diagonal) of its centre can
-// contribute; they form one interval of the sorted reduced angles (two when
-// it wraps past pi), found by binary search.  Each batch of 16 angles stages,
-// per angle, the window of samples the tile can reach; each lane then sums its
-// taps along the ray with the Gaussian weights from a two-ratio recurrence:
-//   w(k+1) = w(k) r(k),  r(k+1) = r(k) exp2(-2 kappa s^2).
-// The tile centre's along-ray position and perpendicular offset are formed in
-// FP64 (integer + FP32 fraction), lanes add only their in-tile offsets, so the
+// The Gaussian's weights depend on the grid point and the sample only, not on
+// the slices, so the sum over the polar samples is a matrix product:
+//   grid[point][column] = sum over (angle, sample) W[point][(angle, sample)] spec[(angle, sample)][column],
+// a column being the real or imaginary part of a pair.  Each slice's spectrum is
+// Hermitian, so the point -u has the weights of u on the mirrored samples: 16
+// columns are the two parts of four pairs at sample k and the same at -k.  One
+// 16x16x32 instruction adds 4 angles x 8 samples for a 4x4 block of points and
+// 16 columns; the weights are formed once for up to 16 pairs.  A block reaches
+// 8.1 samples either way of its centre (half_width 6, one grid point per
+// sample): three such groups of 8 per angle.
+//
+// Precision: weights and samples are two FP16 values each (the rounded value
+// and what it misses) and three products are summed, the dropped one below
+// 2^-22 of the whole; 4 angles at a time are summed from zero and added once, and
+// where more than 128 angles meet (tiles around the origin) FP64 totals take
+// up the FP32 sums every 64 angles.  The weights are not cut off at the
+// truncation radius: every sample that a window holds counts.
+//
+// Work-group: 32x32 points of a tile (or a 16x16 quarter of one that many
+// angles reach) for 4 NT pairs, 16 waves; wave w owns 4 neighbouring blocks (or
+// one).  The grid is periodic (M points per side): the host lists, per tile, the
+// sorted angles that reach it or an image of it shifted by +-M.  Four angles at
+// a time, the samples from 32 before the tile centre's to 31 after (24 and 23)
+// go straight from global memory into one of two LDS buffers while the other is
+// summed; a wave skips the blocks that none of the four angles reaches.  The
+// tile centre's along-ray position and perpendicular offset are formed in FP64
+// (integer + FP32 fraction), lanes add only their in-tile offsets, so the
 // coordinates keep FP32 precision at any grid size.
+//
+// Bound: vector work (weights and their split, 37 instructions per 12 matrix
+// products) and matrix products share a SIMD without hiding each other fully;
+// 16 waves take a tile's 8 blocks of angles (at 2048 angles) in step, each
+// waiting for the busiest.  2048 angles, 32 pairs, 4096^2 grid: 9.5 ms as a
+// gather per grid point and pair, 3.3 ms so; 721 angles, 5 pairs, 2048^2:
+// 0.57 -> 0.29 ms, the longest chain of blocks around the origin.  Tried and not
+// better: wave priorities, all LDS reads of a product group ahead of its weights.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int lower_bound_f(const float* v, int n, float x) {
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (v[mid] < x) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
-__device__ __forceinline__ int upper_bound_f(const float* v, int n, float x) {
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (v[mid] <= x) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
+constexpr int kFrWaves = 16;
+constexpr int kFrAngles = 4;  // per staged block: one per 16 lanes of an operand
+constexpr int kFrChunk = 16;  // blocks whose geometry is formed at a time, one angle per lane
+
+template <int TB> constexpr int fr_slots() { return TB == 32 ? 64 : 48; }
+template <int TB, int NT> constexpr int fr_buffer() { return 2 * (kFrAngles / 2) * NT * kSlotBytes * fr_slots<TB>(); }
+// Image of a tile of one pair while it is stored: rows and images start in other banks.
+template <int TB> constexpr int fr_row() { return 8 * TB + 16; }
+template <int TB> constexpr int fr_image() { return TB * fr_row<TB>() + 64; }
+template <int NT> constexpr size_t fr_grid_lds() {
+    constexpr int stage = 2 * fr_buffer<32, NT>() + 2 * kFrChunk * kFrAngles * 24, store = 2 * kFrPairGroup * fr_image<32>();
+    return stage > store ? stage : store;
 }
 
-template <int NT>
-__global__ void __launch_bounds__(256)
-k_fr_grid(FourierTables t, const float2* __restrict__ spec, float2* __restrict__ grid) {
-    extern __shared__ float4 stage[];  // [kFrBatch][sw]: (sample k, sample -k)
-    __shared__ int s_kc[kFrBatch];
-    __shared__ float4 s_geo[kFrBatch];  // (fraction of the centre's position, perpendicular offset, cos, sin)
-    const int M = t.M, hM = M / 2, tps = M / kFrTile;
-    const int p = blockIdx.x / t.ntiles;
-    const int tile = t.tile_order[blockIdx.x - p * t.ntiles];
-    const int ty = tile / tps, tx = tile - ty * tps;
-    // tile rows ty >= tps/2 (uy >= 0) also produce the mirror points -u;
-    // tile row 0 only supplies the grid row uy = -M/2, which no mirror reaches
-    const bool nyq = ty == 0;
-    const int ux0 = tx * kFrTile - hM, uy0 = ty * kFrTile - hM;
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int ox = (w >> 1) * 8 + (l >> 3), oy = (w & 1) * 8 + (l & 7);
-    // lane and wave-centre offsets from the tile centre
-    const float dx = static_cast<float>(ox) - 7.5f, dy = static_cast<float>(oy) - 7.5f;
-    const float wdx = static_cast<float>((w >> 1) * 8) - 4.0f, wdy = static_cast<float>((w & 1) * 8) - 4.0f;
-    const float2* sp = spec + static_cast<int64_t>(p) * t.na * t.SL;
-    const int h = t.L / 2;
-    const float reach = t.msp + kFrHalfDiag + 1.0f;
-    // each batch of angles is summed in FP32, the batches in FP64: central
-    // grid points collect thousands of angles
-    double ax = 0.0, ay = 0.0, bx = 0.0, by = 0.0;
-    for (int img = 0; img < 9; ++img) {
-        const float Cx = static_cast<float>(ux0 + (img % 3 - 1) * M) + 7.5f;
-        const float Cy = static_cast<float>(uy0 + (img / 3 - 1) * M) + 7.5f;
-        const float rho = sqrtf(Cx * Cx + Cy * Cy);
-        if (rho > static_cast<float>(hM) + reach) continue;  // samples lie within radius M/2
-        int lo0 = 0, hi0 = t.na, lo1 = 0, hi1 = 0;
-        if (rho > reach) {
-            const float d = asinf(reach / rho) + 1e-4f;
-            if (d < 1.5f) {
-                float al = atan2f(Cy, Cx);
-                if (al < 0.0f) al += kPiF;
-                if (al >= kPiF) al -= kPiF;
-                const float lo = al - d, hi = al + d;
-                if (lo < 0.0f) {
-                    lo0 = lower_bound_f(t.beta, t.na, lo + kPiF);
-                    hi1 = upper_bound_f(t.beta, t.na, hi);
-                } else if (hi >= kPiF) {
-                    lo0 = lower_bound_f(t.beta, t.na, lo);
-                    hi1 = upper_bound_f(t.beta, t.na, hi - kPiF);
-                } else {
-                    lo0 = lower_bound_f(t.beta, t.na, lo);
-                    hi0 = upper_bound_f(t.beta, t.na, hi);
-                }
-            }
-        }
-        const double Cxd = static_cast<double>(Cx), Cyd = static_cast<double>(Cy);
-        for (int rr = 0; rr < 2; ++rr) {
-            const int alo = rr ? lo1 : lo0, ahi = rr ? hi1 : hi0;
-            for (int a0 = alo; a0 < ahi; a0 += kFrBatch) {
-                const int cnt = min(kFrBatch, ahi - a0);
-                __syncthreads();  // the previous batch's reads are done
-                if (threadIdx.x < cnt) {
-                    const int ap = a0 + threadIdx.x;
-                    const double cbd = t.cbd[ap], sbd = t.sbd[ap];
-                    const double tc = (Cxd * cbd + Cyd * sbd) * static_cast<double>(t.inv_s);
-                    const double kc = floor(tc);
-                    s_kc[threadIdx.x] = static_cast<int>(kc);
-                    s_geo[threadIdx.x] = make_float4(static_cast<float>(tc - kc),
-                                                     static_cast<float>(Cyd * cbd - Cxd * sbd), t.cb[ap], t.sb[ap]);
-                }
-                __syncthreads();
-                // wave w stages angles w, w + 4, ...; lane l the window's sample l (sw <= 64)
-                for (int j = w; j < cnt; j += 4) {
-                    if (l < t.sw) {
-                        const int k = s_kc[j] - t.back + l;  // signed frequency index
-                        const float2* row = sp + static_cast<int64_t>(a0 + j) * t.SL + h;
-                        const bool in = k >= -h && k <= h;
-                        const float2 v = in ? row[k] : make_float2(0.0f, 0.0f);
-                        const float2 u = in ? row[-k] : make_float2(0.0f, 0.0f);
-                        stage[j * t.sw + l] = make_float4(v.x, v.y, u.x, u.y);
-                    }
-                }
-                __syncthreads();
-                // FP32 partial sums over the batch (at most 16 angles x NT taps)
-                float pa = 0.0f, pb = 0.0f, pc = 0.0f, pd = 0.0f;
-                for (int j = 0; j < cnt; ++j) {
-                    const float4 geo = s_geo[j];
-                    const float cb = geo.z, sb = geo.w, cp = geo.y;
-                    // no lane of this wave within the radius of the ray
-                    if (fabsf(cp + wdy * cb - wdx * sb) > t.msp + kFrWaveHalfDiag + 0.01f) continue;
-                    const float tr = geo.x + (dx * cb + dy * sb) * t.inv_s;  // along-ray, samples, from kc
-                    const float dp = cp + dy * cb - dx * sb;                  // perpendicular, grid points
-                    if (fabsf(dp) > t.msp) continue;  // outside the band: no LDS reads for this lane
-                    const int k0 = coord_floor(tr) - NT / 2 + 1;
-                    const float q = (tr - static_cast<float>(k0)) * t.s;    // distance to tap k0, grid points
-                    // for grid spacings s <= 8 and half widths 3..8 the exponents stay within
-                    // (-80, 70): the hardware exp2 needs no range handling
-                    float wgt = __builtin_amdgcn_exp2f(-t.kappa * (dp * dp + q * q));
-                    float r = __builtin_amdgcn_exp2f(t.kappa * (2.0f * t.s * q - t.s * t.s));
-                    const int idx = min(max(k0 + t.back, 0), t.sw - NT);
-                    const float4* sv = stage + j * t.sw + idx;
+// S1: one grid point per frequency sample (the weights then follow from two
+// exponentials per 8 samples); otherwise one exponential per sample.
+template <int TB, int NT, bool S1>
+__device__ __forceinline__ void gather_tile(const FourierTables& t, const u4_t* __restrict__ spec, int4 item, int group0,
+                                            int pairs, float2* __restrict__ grid, unsigned char* smem) {
+    constexpr int BW = TB == 32 ? 4 : 1;                  // blocks per wave
+    constexpr bool kWide = TB == 16;                       // FP64 totals, every 16 blocks of angles
+    constexpr int WN = fr_slots<TB>(), kBack = WN / 2;
+    constexpr int kTile = kSlotBytes * WN, kPair = NT * kTile, kPlane = (kFrAngles / 2) * kPair;
+    constexpr int kBuf = fr_buffer<TB, NT>(), kParts = kTile / 1024, kLoads = kBuf / 1024;
+    // two chunks of the item's blocks: fraction, offset, cos, sin; frequency of slot 0, angle
+    float4* sGeo = reinterpret_cast<float4*>(smem + 2 * fr_buffer<32, NT>());
+    int2* sRow = reinterpret_cast<int2*>(sGeo + 2 * kFrChunk * kFrAngles);
+    constexpr int kRing = 2 * kFrChunk - 1;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int M = t.M, hM = M / 2, h = t.L / 2;
+    const float mid = 0.5f * (TB - 1);
+
+    f4_t acc[BW][NT];
+    double wide[kWide ? NT : 1][4];
 #pragma unroll
-                    for (int tap = 0; tap < NT; ++tap) {
-                        const float4 v = sv[tap];
-                        pa = __builtin_fmaf(wgt, v.x, pa);
-                        pb = __builtin_fmaf(wgt, v.y, pb);
-                        pc = __builtin_fmaf(wgt, v.z, pc);
-                        pd = __builtin_fmaf(wgt, v.w, pd);
-                        if (tap + 1 < NT) {
-                            wgt *= r;
-                            r *= t.ratio2;
-                        }
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+#pragma unroll
+            for (int i = 0; i < BW; ++i) acc[i][n][r] = 0.0f;
+            if (kWide) wide[n][r] = 0.0;
+        }
+    // FP64 totals: what has been summed in FP32 since the last time
+    auto carry = [&]() {
+#pragma unroll
+        for (int n = 0; n < (kWide ? NT : 0); ++n)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                wide[n][r] += static_cast<double>(acc[0][n][r]);
+                acc[0][n][r] = 0.0f;
+            }
+    };
+
+    const int nblk = item.w;
+    // Geometry of the angles of a chunk of blocks, one per lane of wave 0.
+    auto geometry = [&](int chunk) {
+        const int b = chunk * kFrChunk + (lane >> 2), j = lane & 3;
+        if (b >= nblk) return;
+        const int4 blk = t.blocks[item.z + b];
+        const bool on = j < blk.y;
+        const int a = blk.x + (on ? j : 0);
+        const double Cx = static_cast<double>(__int_as_float(blk.z)), Cy = static_cast<double>(__int_as_float(blk.w));
+        const double c = t.cbd[a], sn = t.sbd[a];
+        const double tc = (Cx * c + Cy * sn) * static_cast<double>(t.inv_s);
+        const double kc = floor(tc);
+        const int e = (chunk & 1) * kFrChunk * kFrAngles + lane;
+        // no angle: an offset that every weight vanishes at, samples off every row
+        sGeo[e] = make_float4(static_cast<float>(tc - kc), on ? static_cast<float>(Cy * c - Cx * sn) : 1e9f,
+                              static_cast<float>(c), static_cast<float>(sn));
+        sRow[e] = make_int2(on ? static_cast<int>(kc) - kBack : 1 << 28, a);
+    };
+    // Staging: each load of a wave moves 1 KiB of LDS, 16 samples of four pairs
+    // (16 bytes of sample k, 16 of sample -k) for two angles: a uniform base
+    // (row of the first angle) and a 32-bit offset per lane, 0 off the row's ends.
+    const int flip = lane & 1 ? -1 : 0;
+    const uint32_t pair_off = (lane & 2 ? 2u * static_cast<uint32_t>(t.SL) : 0u) * 16u + 16u * static_cast<uint32_t>(h + 1);
+    const uint32_t lds0 = lds_address(smem);
+    const int last_group = (pairs - 1) / kFrPairGroup;
+    auto stage = [&](int k) {
+        const int2* rows = sRow + (k & kRing) * kFrAngles;
+#pragma unroll
+        for (int s = 0; s < (kLoads + kFrWaves - 1) / kFrWaves; ++s) {
+            const int i = s * kFrWaves + wv;
+            if (kLoads % kFrWaves != 0 && i >= kLoads) break;
+            const int part = i % kParts, n = i / kParts % NT, pr = i / (kParts * NT) % (kFrAngles / 2),
+                      pl = i / (kParts * NT * (kFrAngles / 2));
+            const int a = __builtin_amdgcn_readfirstlane(rows[2 * pr].y);
+            const int kk = rows[2 * pr + ((lane >> 1) & 1)].x + 16 * part + (lane >> 2);
+            const bool in = static_cast<uint32_t>(kk + h) <= static_cast<uint32_t>(2 * h);
+            const uint32_t off = static_cast<uint32_t>((kk ^ flip) - flip) * 16u + pair_off;
+            // pairs past the last are read from its group again; their sums are never stored
+            const int g = min(group0 + n, last_group);
+            load_lds16(spec + ((static_cast<int64_t>(g) * t.na + a) * 2 + pl) * t.SL, in ? off : 0u,
+                       lds0 + (k & 1) * kBuf + i * 1024);
+        }
+    };
+
+    // points of the wave's blocks: operand row m = lane % 16 is point (m / 4, m % 4) of a block
+    const int px = (lane >> 2) & 3, py = lane & 3, ag = lane >> 4;
+    // block i of the wave starts at (bx + 16 (i / 2), by + 16 (i % 2)): any strip
+    // of a ray's width meets about half the blocks of every wave
+    const int bx = 4 * (wv >> 2), by = TB == 32 ? 4 * ((wv + (wv >> 2)) & 3) : 4 * (wv & 3);
+    const float dx = static_cast<float>(bx + px) - mid, dy = static_cast<float>(by + py) - mid;
+    const float cx = uniform(static_cast<float>(bx) + 1.5f - mid), cy = uniform(static_cast<float>(by) + 1.5f - mid);
+    const float half = uniform(4.0f * static_cast<float>(t.units)), reach = uniform(t.msp + 2.1313f);
+    const float kap = t.kappa, kap2 = uniform(2.0f * kap), s1 = t.s, step = uniform(8.0f * s1);
+    // the transposing read takes slot (lane / 4) % 4 of 4 from this lane's address
+    const uint32_t lane_buf = lds0 + (ag >> 1) * kPair + (ag & 1) * 32 + 8 * (lane & 3) +
+                                    kSlotBytes * (kBack + ((lane >> 2) & 3));
+
+    if (wv == 0) geometry(0);
+    __syncthreads();
+    if (nblk > 0) stage(0);
+    wait_loads();
+    __syncthreads();
+    for (int k = 0; k < nblk; ++k) {
+        // the geometry first: the loads into LDS that follow complete in order,
+        // and nothing before the end of the block waits for them
+        if (wv == 0 && k % kFrChunk == 0) geometry(k / kFrChunk + 1);
+        if (k + 1 < nblk) stage(k + 1);
+        const float4 ge = sGeo[(k & kRing) * kFrAngles + ag];
+        const float cb = ge.z, sb = ge.w;
+        // block 0 of the wave: its centre's offset from the ray and position on
+        // it, and the same for this lane's point
+        const float oc = ge.y + cy * cb - cx * sb;
+        const float tc = __builtin_fmaf(__builtin_fmaf(cx, cb, cy * sb), t.inv_s, ge.x);
+        const float op = ge.y + dy * cb - dx * sb;
+        const float tp = __builtin_fmaf(__builtin_fmaf(dx, cb, dy * sb), t.inv_s, ge.x);
+#pragma unroll
+        for (int i = 0; i < BW; ++i) {
+            const float ex = 16.0f * (i >> 1), ey = 16.0f * (i & 1);
+            const float across = ey * cb - ex * sb, along = __builtin_fmaf(ex, cb, ey * sb);
+            // does any of the four rays pass within the radius of a point of the block?
+            if (!__any(fabsf(oc + across) <= reach)) continue;
+            const int st = coord_floor(__builtin_fmaf(along, t.inv_s, tc) - half);  // first sample of the window, from the centre's
+            const float tr = __builtin_fmaf(along, t.inv_s, tp), dp = op + across;
+            const float q0 = (tr - static_cast<float>(st)) * s1;        // distance to the first sample, grid points
+            const float e0 = -kap * dp * dp;
+            uint32_t rowp = opaque(lane_buf + (k & 1) * kBuf + kSlotBytes * st);
+            f4_t sum[NT];
+            // 8 samples from distance q: weights in two FP16 values, then NT products of three
+            auto unit = [&](auto first, float q, uint32_t src) {
+                float w[8];
+                if constexpr (S1) {
+                    // the recurrence starts anew every 8 samples: a start that
+                    // underflows (14 or more grid points away) has no weight
+                    // above 2^-30 in its 8 samples
+                    float v = __builtin_amdgcn_exp2f(__builtin_fmaf(-kap * q, q, e0));
+                    float ratio = __builtin_amdgcn_exp2f(__builtin_fmaf(kap2, q, -kap));
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        w[j] = v;
+                        v *= ratio;
+                        ratio *= t.ratio2;
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const float qj = __builtin_fmaf(-static_cast<float>(j), s1, q);
+                        w[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(-kap * qj, qj, e0));
                     }
                 }
-                ax += static_cast<double>(pa);
-                ay += static_cast<double>(pb);
-                bx += static_cast<double>(pc);
-                by += static_cast<double>(pd);
+                u4_t hi, lo;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t a, b;
+                    split_pair(w[2 * j], w[2 * j + 1], a, b);
+                    hi[j] = a;
+                    lo[j] = b;
+                }
+#pragma unroll
+                for (int n = 0; n < NT; ++n) {
+                    const u4_t x = read_slots(src + n * kTile), y = read_slots(src + n * kTile + kPlane);
+                    if constexpr (first.value) sum[n] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
+                    sum[n] = mfma16(lo, x, sum[n]);  // smallest products first
+                    sum[n] = mfma16(hi, y, sum[n]);
+                    sum[n] = mfma16(hi, x, sum[n]);
+                }
+            };
+            unit(std::true_type{}, q0, rowp);
+            float q = q0;
+#pragma unroll 1
+            for (int u = 1; u < t.units; ++u) {
+                q -= step;
+                rowp = opaque(rowp + 8 * kSlotBytes);
+                unit(std::false_type{}, q, rowp);
+            }
+#pragma unroll
+            for (int n = 0; n < NT; ++n)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][n][r] += sum[n][r];
+        }
+        if (kWide && k % 16 == 15) carry();
+        wait_loads();  // this wave's part of block k + 1 is in LDS
+        __syncthreads();
+    }
+
+    // Result: lane l holds column l % 16 (part l & 1 of pair (l / 2) % 4, mirrored
+    // for l & 8) of points (l / 16, 0 .. 3) of each block.  Neighbouring lanes
+    // exchange parts (the even one keeps points 0 and 1, the odd one 2 and 3), and
+    // the four pairs of a group go through LDS to be stored a tile row at a time.
+    // A mirrored row is kept from its end, in the order of its addresses.
+    carry();
+    constexpr int kRow = fr_row<TB>(), kImage = fr_image<TB>();
+    const bool odd = lane & 1, mirror = lane & 8;
+    const bool nyq = item.y == -hM;  // this tile row only supplies the grid row uy = -M/2, which no mirror reaches
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+        if ((group0 + n) * kFrPairGroup >= pairs) break;
+        if (n > 0) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < BW; ++i) {
+            float v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = kWide ? static_cast<float>(wide[kWide ? n : 0][r]) : acc[i][n][r];
+            const float x0 = __shfl_xor(odd ? v[0] : v[2], 1), x1 = __shfl_xor(odd ? v[1] : v[3], 1);
+            const float2 c0 = odd ? make_float2(x0, v[2]) : make_float2(v[0], x0);
+            const float2 c1 = odd ? make_float2(x1, v[3]) : make_float2(v[1], x1);
+            const int y = by + 16 * (i & 1) + (odd ? 2 : 0);  // even
+            unsigned char* row = smem + (((lane >> 1) & 3) + (mirror ? 4 : 0)) * kImage + (bx + 16 * (i >> 1) + ag) * kRow;
+            *reinterpret_cast<float4*>(row + 8 * (mirror ? TB - 2 - y : y)) =
+                mirror ? make_float4(c1.x, c1.y, c0.x, c0.y) : make_float4(c0.x, c0.y, c1.x, c1.y);
+        }
+        __syncthreads();
+        constexpr int kPer = TB / 2;  // threads per row of TB points
+#pragma unroll
+        for (int q = tid; q < 8 * TB * kPer; q += 64 * kFrWaves) {
+            const int y = 2 * (q % kPer), x = q / kPer % TB, img = q / (kPer * TB);
+            const int p = (group0 + n) * kFrPairGroup + (img & 3);
+            if (p >= pairs) continue;
+            const float4 v = *reinterpret_cast<const float4*>(smem + img * kImage + x * kRow + 8 * y);
+            const int ux = item.x + x;
+            float2* plane = grid + static_cast<int64_t>(p) * M * M;
+            if (img < 4) {
+                float2* g = plane + static_cast<int64_t>(ux & (M - 1)) * M + ((item.y + y) & (M - 1));
+                if (!nyq) *reinterpret_cast<float4*>(g) = v;
+                else if (item.y + y == -hM) *g = make_float2(v.x, v.y);
+            } else if (!nyq) {
+                // points uy = item.y + TB - 1 - y and the one below it, mirrored
+                const int uy = -(item.y + TB - 1 - y);
+                float2* g = plane + static_cast<int64_t>((-ux) & (M - 1)) * M;
+                g[uy & (M - 1)] = make_float2(v.x, v.y);
+                if (uy + 1 < 0) g[(uy + 1) & (M - 1)] = make_float2(v.z, v.w);  // the row uy = 0 is its own mirror
             }
         }
     }
-    const int ux = ux0 + ox, uy = uy0 + oy;
-    if (nyq) {
-        if (uy == -hM) grid[(static_cast<int64_t>(p) * M + (ux & (M - 1))) * M + (uy & (M - 1))] =
-            make_float2(static_cast<float>(ax), static_cast<float>(ay));
-        return;
-    }
-    grid[(static_cast<int64_t>(p) * M + (ux & (M - 1))) * M + (uy & (M - 1))] =
-        make_float2(static_cast<float>(ax), static_cast<float>(ay));
-    if (uy > 0)  // the row uy = 0 is its own mirror
-        grid[(static_cast<int64_t>(p) * M + ((-ux) & (M - 1))) * M + ((-uy) & (M - 1))] =
-            make_float2(static_cast<float>(bx), static_cast<float>(by));
+}
+
+template <int NT, bool S1>
+__global__ void __launch_bounds__(64 * kFrWaves)
+k_fr_grid(FourierTables t, const u4_t* __restrict__ spec, int pairs, int groups, float2* __restrict__ grid) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int it = blockIdx.x / groups, group0 = (blockIdx.x - it * groups) * NT;
+    const int4 item = t.items[it];
+    if (it < t.n_small)
+        gather_tile<16, NT, S1>(t, spec, item, group0, pairs, grid, smem);
+    else
+        gather_tile<32, NT, S1>(t, spec, item, group0, pairs, grid, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -354,13 +528,14 @@ constexpr int kFrAnglesPerGroup = 8;
 template <int L>
 __global__ void __launch_bounds__(L / kRegPts)
 k_fr_spectra_reg(RawInput in, int rows, const float* __restrict__ dmean, const float* __restrict__ rden,
-                 const float2* __restrict__ tw, FourierTables t, float2* __restrict__ spec) {
+                 const float2* __restrict__ tw, FourierTables t, uint32_t* __restrict__ spec) {
     extern __shared__ float2 lds[];
     constexpr int B = L / kRegPts, h = L / 2;
     const int n = t.n, off = (L - n) / 2;
-    const int groups = (t.na + kFrAnglesPerGroup - 1) / kFrAnglesPerGroup;
-    const int p = blockIdx.x / groups;
-    const int a0 = (blockIdx.x - p * groups) * kFrAnglesPerGroup;
+    int p, a0;
+    spectra_work((rows + 1) / 2, (t.na + kFrAnglesPerGroup - 1) / kFrAnglesPerGroup, p, a0);
+    if (2 * p >= rows) return;  // whole work-group
+    a0 *= kFrAnglesPerGroup;
     const int a1 = min(t.na, a0 + kFrAnglesPerGroup);
     const int z0 = 2 * p;
     const bool has1 = z0 + 1 < rows;
@@ -397,13 +572,14 @@ k_fr_spectra_reg(RawInput in, int rows, const float* __restrict__ dmean, const f
         reg_fft<L>(x, lds, tw, tid);
         const int sl = t.slot[a];
         const bool rev = (sl & 1) != 0;
-        float2* row = spec + (static_cast<int64_t>(p) * t.na + (sl >> 1)) * t.SL;
+        uint32_t* row = spectra_row(spec, p, sl >> 1, t);
+        if (tid == 0) spectra_zero(row, t.SL);
 #pragma unroll
         for (int s = 0; s < kRegPts; ++s) {
             const int m = tid + B * s;
             const int k = m < h ? m : m - L;
-            row[(rev ? -k : k) + h] = cmul(x[s], t.E[k + h]);
-            if (m == h) row[(rev ? -h : h) + h] = cmul(x[s], t.E[L]);
+            spectra_store(row, (rev ? -k : k) + h + 1, t.SL, cmul(x[s], t.E[k + h]));
+            if (m == h) spectra_store(row, (rev ? -h : h) + h + 1, t.SL, cmul(x[s], t.E[L]));
         }
 #pragma unroll
         for (int s = 0; s < kRegPts; ++s) cur[s] = nxt[s];
@@ -487,25 +663,33 @@ k_fr_cols_reg(const float2* __restrict__ cols, const float2* __restrict__ tw, Fo
 
 size_t reg_lds(int L) { return static_cast<size_t>(L + L / 16) * sizeof(float2); }
 
-template <int NT>
-hipError_t launch_grid_nt(const FourierTables& t, const float2* spec, int pairs, float2* grid, hipStream_t st) {
-    const size_t lds = static_cast<size_t>(kFrBatch) * t.sw * sizeof(float4);
-    hipError_t e = fr_lds(k_fr_grid<NT>, lds);
+template <int NT, bool S1>
+hipError_t launch_grid_t(const FourierTables& t, const uint32_t* spec, int pairs, float2* grid, hipStream_t st) {
+    constexpr size_t lds = fr_grid_lds<NT>();
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
+    hipError_t e = fr_lds(k_fr_grid<NT, S1>, lds);
     if (e != hipSuccess) return e;
-    const dim3 g(static_cast<unsigned>(static_cast<int64_t>(pairs) * t.ntiles));
-    hipLaunchKernelGGL((k_fr_grid<NT>), g, dim3(256), lds, st, t, spec, grid);
+    const int groups = (pairs + kFrPairGroup * NT - 1) / (kFrPairGroup * NT);
+    const dim3 g(static_cast<unsigned>(static_cast<int64_t>(t.n_items) * groups));
+    hipLaunchKernelGGL((k_fr_grid<NT, S1>), g, dim3(64 * kFrWaves), lds, st, t, reinterpret_cast<const u4_t*>(spec), pairs,
+                       groups, grid);
     return hipGetLastError();
+}
+
+template <int NT>
+hipError_t launch_grid_nt(const FourierTables& t, const uint32_t* spec, int pairs, float2* grid, hipStream_t st) {
+    return t.s == 1.0f ? launch_grid_t<NT, true>(t, spec, pairs, grid, st)
+                       : launch_grid_t<NT, false>(t, spec, pairs, grid, st);
 }
 
 }  // namespace
 
 hipError_t launch_fourier_spectra(const RawInput& in, int rows, const float* dmean, const float* rden,
-                                  const float2* tw_L, const FourierTables& t, float2* spec, hipStream_t st) {
+                                  const float2* tw_L, const FourierTables& t, uint32_t* spec, hipStream_t st) {
     const int pairs = (rows + 1) / 2;
 #define TP_FR_REG(LL)                                                                                      \
     case LL: {                                                                                            \
-        const int64_t ag = (t.na + kFrAnglesPerGroup - 1) / kFrAnglesPerGroup;                             \
-        const dim3 g(static_cast<unsigned>(static_cast<int64_t>(pairs) * ag));                            \
+        const dim3 g(spectra_grid(pairs, (t.na + kFrAnglesPerGroup - 1) / kFrAnglesPerGroup));            \
         const hipError_t e = fr_lds(k_fr_spectra_reg<LL>, reg_lds(LL));                                   \
         if (e != hipSuccess) return e;                                                                    \
         hipLaunchKernelGGL((k_fr_spectra_reg<LL>), g, dim3(LL / kRegPts), reg_lds(LL), st, in, rows, dmean, rden, \
@@ -523,28 +707,16 @@ hipError_t launch_fourier_spectra(const RawInput& in, int rows, const float* dme
     const size_t lds = static_cast<size_t>(t.L) * sizeof(float2);
     hipError_t e = fr_lds(k_fr_spectra, lds);
     if (e != hipSuccess) return e;
-    const dim3 grid(static_cast<unsigned>(static_cast<int64_t>(pairs) * t.na));
+    const dim3 grid(spectra_grid(pairs, t.na));
     hipLaunchKernelGGL(k_fr_spectra, grid, dim3(fr_block(t.L)), lds, st, in, rows, dmean, rden, tw_L, t, spec);
     return hipGetLastError();
 }
 
-size_t fourier_grid_tiles(int M) {
-    const size_t tps = static_cast<size_t>(M) / kFrTile;
-    return tps * (tps / 2) + tps;  // rows with uy >= 0, plus the row holding uy = -M/2
-}
-
-hipError_t launch_fourier_grid(const FourierTables& t, const float2* spec, int pairs, float2* grid, hipStream_t st) {
-    switch (t.nt) {
-        case 2: return launch_grid_nt<2>(t, spec, pairs, grid, st);
-        case 4: return launch_grid_nt<4>(t, spec, pairs, grid, st);
-        case 6: return launch_grid_nt<6>(t, spec, pairs, grid, st);
-        case 8: return launch_grid_nt<8>(t, spec, pairs, grid, st);
-        case 10: return launch_grid_nt<10>(t, spec, pairs, grid, st);
-        case 12: return launch_grid_nt<12>(t, spec, pairs, grid, st);
-        case 14: return launch_grid_nt<14>(t, spec, pairs, grid, st);
-        case 16: return launch_grid_nt<16>(t, spec, pairs, grid, st);
-        default: return hipErrorInvalidValue;
-    }
+// As many pairs per work-group as there are, up to 16: they share the weights.
+hipError_t launch_fourier_grid(const FourierTables& t, const uint32_t* spec, int pairs, float2* grid, hipStream_t st) {
+    if (pairs > 2 * kFrPairGroup) return launch_grid_nt<4>(t, spec, pairs, grid, st);
+    return pairs > kFrPairGroup ? launch_grid_nt<2>(t, spec, pairs, grid, st)
+                                : launch_grid_nt<1>(t, spec, pairs, grid, st);
 }
 
 hipError_t launch_fourier_rows(const FourierTables& t, const float2* tw_M, const float2* grid, int pairs,

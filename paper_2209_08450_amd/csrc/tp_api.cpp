@@ -265,8 +265,11 @@ tp_status check_raw(const uint16_t* proj, const uint16_t* dark, int32_t n_dark, 
 // ---- Fourier-domain backprojection: sizes, tables, workspace layout ----
 constexpr int kFourierDefaultHalfWidth = 6;
 constexpr int kFourierMaxSide = 16384;
-// Tile half-diagonal (7.5 sqrt(2)) of the gather's 16x16 tiles, as in the kernel.
-constexpr double kFrHalfDiag = 10.606601717798213;
+// The gather sums 32x32 tiles of grid points with one work-group; tiles that
+// more angles reach than this (those around the origin) are cut in four, so
+// that none holds up the launch (2048 angles, 16 pairs: 1.1 ms for the longest
+// quarter, 512 blocks of 4 angles one after the other).
+constexpr int kFrSplitAngles = 128;
 
 struct FrDims {
     int L, M, SL, ng;  // pad length, grid side, samples per spectrum row, 16-row column groups
@@ -277,12 +280,19 @@ FrDims fr_dims(const tp_plan* plan) {
     FrDims d{};
     d.L = plan->filt.L;
     d.M = std::max({d.L, 1 << ilog2(2 * static_cast<int64_t>(plan->N)), 64});
-    d.SL = d.L + 1;
+    d.SL = d.L + 2;
     d.ng = (plan->N + 15) / 16;
     d.spec_pair = static_cast<size_t>(plan->na) * d.SL * sizeof(float2);
     d.cols_pair = static_cast<size_t>(d.ng) * 16 * d.M * sizeof(float2);
     d.grid_pair = static_cast<size_t>(d.M) * d.M * sizeof(float2);
     return d;
+}
+
+// Bytes of the region that holds a pass's spectra (pairs in fours) and later
+// its column-group intermediate.
+size_t fr_region_a(const FrDims& d, int64_t P) {
+    const size_t spec = static_cast<size_t>((P + tp::kFrPairGroup - 1) / tp::kFrPairGroup * tp::kFrPairGroup) * d.spec_pair;
+    return align256(std::max(spec, static_cast<size_t>(P) * d.cols_pair));
 }
 
 // Workspace: dark/flat tables of every row, then (per pass of P pairs) a
@@ -291,8 +301,7 @@ FrDims fr_dims(const tp_plan* plan) {
 size_t fr_workspace(const tp_plan* plan, int32_t n_rows, int64_t P) {
     const FrDims d = fr_dims(plan);
     return tp_normalize_workspace_bytes(n_rows, plan->n) +
-           align256(static_cast<size_t>(P) * std::max(d.spec_pair, d.cols_pair)) +
-           align256(static_cast<size_t>(P) * d.grid_pair);
+           fr_region_a(d, P) + align256(static_cast<size_t>(P) * d.grid_pair);
 }
 
 tp_status fourier_tables(const tp_plan* plan, tp_filter_kind kind, int msp, tp::FourierTables* out,
@@ -316,31 +325,37 @@ tp_status fourier_tables(const tp_plan* plan, tp_filter_kind kind, int msp, tp::
     const double s = static_cast<double>(M) / L;
     const double tau = msp / (2.0 * std::sqrt(2.0) * M_PI);
     const double kappa = 1.0 / (4.0 * tau * std::log(2.0));
-    const int nt = 2 * static_cast<int>(std::ceil(msp / s));
-    const int back = static_cast<int>(std::ceil((kFrHalfDiag + 1.0) / s)) + nt / 2;
-    const int sw = static_cast<int>(std::ceil(2.0 * (kFrHalfDiag + 1.0) / s)) + nt + 4;
-    if (s > 8.0 || sw > 64)
+    // a 4x4 block reaches (1.5 sqrt(2) + msp) / s samples either way of its
+    // centre; the window of 8 units samples starts up to one early
+    const double ext = (1.5 * std::sqrt(2.0) + msp) / s;
+    const int units = static_cast<int>(std::ceil((ext + 1.85) / 4.0));
+    if (s > 8.0 || units > 3)
         return fail(TP_EUNSUPPORTED, "Fourier grid of %d points per side for pad length %d (more than 8 grid "
                     "points per frequency sample)", M, L);
     const double pos0 = plan->center + (L - n) / 2;
     // E[k + L/2] = (pi / na) / L * w_k * H[k] * exp(2 pi i k pos0 / L)
     std::vector<double> H;
     filter_response_fp64(L, kind, H);
+    // a row's samples stay below sqrt(2) 13.82 L (two rows of -ln t, t >= 1e-6),
+    // so 2^(2 e) times them times |E| below 2^15
+    double hmax = 0.0;
+    for (double v : H) hmax = std::max(hmax, std::fabs(v));
+    const int e = static_cast<int>(std::floor(0.5 * std::log2(32768.0 / (M_PI / na * hmax * 1.4143 * 13.82))));
     std::vector<float2> E(static_cast<size_t>(L) + 1);
     for (int k = -h; k <= h; ++k) {
         const double wk = (k == -h || k == h) ? 0.5 : 1.0;
-        const double amp = (M_PI / na) / L * wk * H[static_cast<size_t>((k + L) % L)];
+        const double amp = std::ldexp((M_PI / na) / L * wk * H[static_cast<size_t>((k + L) % L)], 2 * e);
         double fr = static_cast<double>(k) * pos0 / L;
         fr -= std::floor(fr);
         const double ph = 2.0 * M_PI * fr;
         E[static_cast<size_t>(k + h)] =
             make_float2(static_cast<float>(amp * std::cos(ph)), static_cast<float>(amp * std::sin(ph)));
     }
-    // D[i] = 1 / phi_hat((i - N/2) / M), phi_hat(v) = sqrt(4 pi tau) exp(-4 pi^2 tau v^2)
+    // D[i] = 2^-e / phi_hat((i - N/2) / M), phi_hat(v) = sqrt(4 pi tau) exp(-4 pi^2 tau v^2)
     std::vector<float> D(N);
     for (int i = 0; i < N; ++i) {
         const double v = static_cast<double>(i - N / 2) / M;
-        D[i] = static_cast<float>(std::exp(4.0 * M_PI * M_PI * tau * v * v) / std::sqrt(4.0 * M_PI * tau));
+        D[i] = static_cast<float>(std::ldexp(std::exp(4.0 * M_PI * M_PI * tau * v * v) / std::sqrt(4.0 * M_PI * tau), -e));
     }
     // angles reduced modulo pi into [0, pi), sorted; reversed when the reduction was by an odd multiple of pi
     std::vector<double> beta(na);
@@ -355,76 +370,142 @@ tp_status fourier_tables(const tp_plan* plan, tp_filter_kind kind, int msp, tp::
         idx[a] = a;
     }
     std::sort(idx.begin(), idx.end(), [&](int p, int q) { return beta[p] < beta[q] || (beta[p] == beta[q] && p < q); });
-    std::vector<double> cbd(na), sbd(na);
-    std::vector<float> cb(na), sb(na), bf(na);
+    std::vector<double> cbd(na), sbd(na), sorted(na);
     std::vector<int> slot(na);
     for (int j = 0; j < na; ++j) {
         const int a = idx[j];
         cbd[j] = std::cos(beta[a]);
         sbd[j] = std::sin(beta[a]);
-        cb[j] = static_cast<float>(cbd[j]);
-        sb[j] = static_cast<float>(sbd[j]);
-        bf[j] = static_cast<float>(beta[a]);
+        sorted[j] = beta[a];
         slot[a] = 2 * j + rev[a];
     }
-    // The gather's 16x16 work tiles: the tile rows with uy >= 0 (each also
-    // produces the mirror points -u) and tile row 0 (for the grid row
-    // uy = -M/2), nearest the origin first: their angle lists are the longest.
-    const int tps = M / 16;
-    std::vector<int> tiles;
-    tiles.reserve(tp::fourier_grid_tiles(M));
-    for (int ty = 0; ty < tps; ++ty) {
-        if (ty != 0 && ty < tps / 2) continue;
-        for (int tx = 0; tx < tps; ++tx) tiles.push_back(ty * tps + tx);
-    }
-    const int ntiles = static_cast<int>(tiles.size());
-    auto dist = [&](int i) {
-        const double cx = (i % tps) * 16 - M / 2 + 7.5, cy = (i / tps) * 16 - M / 2 + 7.5;
-        return cx * cx + cy * cy;
+    // The gather's work items: 32x32 tiles with uy >= 0 (each also produces the
+    // mirror points -u) and the tile row that holds the grid row uy = -M/2, cut
+    // in four where many angles reach them.  A tile is reached by the angles
+    // whose ray passes within (radius + half-diagonal) of its centre or of its
+    // images shifted by M (the grid is periodic): intervals of the sorted angles.
+    struct Item {
+        int4 v;
+        int64_t angles;
     };
-    std::sort(tiles.begin(), tiles.end(),
-              [&](int p, int q) { return dist(p) < dist(q) || (dist(p) == dist(q) && p < q); });
+    std::vector<Item> small, large;
+    std::vector<int4> blocks;
+    auto ranges_of = [&](int ux0, int uy0, int edge, std::vector<int4>& out) {
+        out.clear();
+        int64_t total = 0;
+        const double mid = 0.5 * (edge - 1), reach = msp + mid * std::sqrt(2.0) + 1.0;
+        for (int img = 0; img < 9; ++img) {
+            const double Cx = ux0 + (img % 3 - 1) * M + mid, Cy = uy0 + (img / 3 - 1) * M + mid;
+            const double rho = std::hypot(Cx, Cy);
+            if (rho > M / 2 + reach) continue;  // samples lie within radius M/2
+            auto add = [&](double lo, double hi) {
+                const int a0 = static_cast<int>(std::lower_bound(sorted.begin(), sorted.end(), lo) - sorted.begin());
+                const int a1 = static_cast<int>(std::upper_bound(sorted.begin(), sorted.end(), hi) - sorted.begin());
+                if (a0 >= a1) return;
+                int4 r;
+                r.x = a0;
+                r.y = a1;
+                const float fx = static_cast<float>(Cx), fy = static_cast<float>(Cy);  // exact: half integers
+                std::memcpy(&r.z, &fx, 4);
+                std::memcpy(&r.w, &fy, 4);
+                out.push_back(r);
+                total += a1 - a0;
+            };
+            const double d = rho > reach ? std::asin(reach / rho) + 1e-4 : 2.0;
+            if (d >= 1.5) {
+                add(-1.0, 4.0);
+                continue;
+            }
+            double al = std::atan2(Cy, Cx);
+            if (al < 0.0) al += M_PI;
+            if (al >= M_PI) al -= M_PI;
+            const double lo = al - d, hi = al + d;
+            if (lo < 0.0) {
+                add(lo + M_PI, 4.0);
+                add(-1.0, hi);
+            } else if (hi >= M_PI) {
+                add(lo, 4.0);
+                add(-1.0, hi - M_PI);
+            } else {
+                add(lo, hi);
+            }
+        }
+        return total;
+    };
+    auto push = [&](std::vector<Item>& to, int ux0, int uy0, const std::vector<int4>& r, int64_t total) {
+        const int first = static_cast<int>(blocks.size());
+        for (const int4& v : r)
+            for (int a = v.x; a < v.y; a += 4) blocks.push_back(make_int4(a, std::min(4, v.y - a), v.z, v.w));
+        to.push_back(Item{make_int4(ux0, uy0, first, static_cast<int>(blocks.size()) - first), total});
+    };
+    std::vector<int4> rs;
+    for (int ty = 0; ty < M / 32; ++ty) {
+        const int uy0 = 32 * ty - M / 2;
+        if (ty != 0 && uy0 < 0) continue;
+        for (int tx = 0; tx < M / 32; ++tx) {
+            const int ux0 = 32 * tx - M / 2;
+            const int64_t total = ranges_of(ux0, uy0, 32, rs);
+            if (total <= kFrSplitAngles) {
+                push(large, ux0, uy0, rs, total);
+                continue;
+            }
+            for (int q = 0; q < 4; ++q) {
+                const int sx = ux0 + 16 * (q & 1), sy = uy0 + 16 * (q >> 1);
+                if (ty == 0 && sy != -M / 2) continue;  // only the row uy = -M/2 is wanted there
+                const int64_t n4 = ranges_of(sx, sy, 16, rs);
+                push(small, sx, sy, rs, n4);
+            }
+        }
+    }
+    auto longest = [](const Item& p, const Item& q) {
+        return p.angles != q.angles ? p.angles > q.angles
+                                    : (p.v.y != q.v.y ? p.v.y < q.v.y : p.v.x < q.v.x);
+    };
+    std::sort(small.begin(), small.end(), longest);
+    std::sort(large.begin(), large.end(), longest);
+    std::vector<int4> items;
+    for (const Item& it : small) items.push_back(it.v);
+    for (const Item& it : large) items.push_back(it.v);
+    if (blocks.empty()) blocks.push_back(make_int4(0, 0, 0, 0));
 
     const size_t sE = align256(sizeof(float2) * E.size()), sD = align256(sizeof(float) * N);
-    const size_t sd = align256(sizeof(double) * na), sf = align256(sizeof(float) * na);
-    const size_t sT = align256(sizeof(int) * ntiles);
-    const size_t total = sE + sD + 2 * sd + 4 * sf + sT;
+    const size_t sd = align256(sizeof(double) * na), sf = align256(sizeof(int) * na);
+    const size_t sI = align256(sizeof(int4) * items.size()), sB = align256(sizeof(int4) * blocks.size());
+    const size_t total = sE + sD + 2 * sd + sf + sI + sB;
     FourierEntry fe;
-    hipError_t e = hipMalloc(&fe.block, total);
-    if (e != hipSuccess) return fail(TP_ENOMEM, "hipMalloc(Fourier tables, %zu bytes): %s", total, hipGetErrorString(e));
+    hipError_t err = hipMalloc(&fe.block, total);
+    if (err != hipSuccess)
+        return fail(TP_ENOMEM, "hipMalloc(Fourier tables, %zu bytes): %s", total, hipGetErrorString(err));
     char* b = static_cast<char*>(fe.block);
     char* dE = b;
     char* dD = dE + sE;
     char* dcbd = dD + sD;
     char* dsbd = dcbd + sd;
-    char* dcb = dsbd + sd;
-    char* dsb = dcb + sf;
-    char* dbeta = dsb + sf;
-    char* dslot = dbeta + sf;
-    char* dtile = dslot + sf;
-    e = hipMemcpy(dE, E.data(), sizeof(float2) * E.size(), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(dD, D.data(), sizeof(float) * N, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(dcbd, cbd.data(), sizeof(double) * na, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(dsbd, sbd.data(), sizeof(double) * na, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(dcb, cb.data(), sizeof(float) * na, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(dsb, sb.data(), sizeof(float) * na, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(dbeta, bf.data(), sizeof(float) * na, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(dslot, slot.data(), sizeof(int) * na, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(dtile, tiles.data(), sizeof(int) * ntiles, hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
+    char* dslot = dsbd + sd;
+    char* ditem = dslot + sf;
+    char* dblock = ditem + sI;
+    auto copy = [&](char* dst, const void* src, size_t bytes) {
+        if (err == hipSuccess) err = hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
+    };
+    copy(dE, E.data(), sizeof(float2) * E.size());
+    copy(dD, D.data(), sizeof(float) * N);
+    copy(dcbd, cbd.data(), sizeof(double) * na);
+    copy(dsbd, sbd.data(), sizeof(double) * na);
+    copy(dslot, slot.data(), sizeof(int) * na);
+    copy(ditem, items.data(), sizeof(int4) * items.size());
+    copy(dblock, blocks.data(), sizeof(int4) * blocks.size());
+    if (err != hipSuccess) {
         (void)hipFree(fe.block);
-        return hip_fail(e, "hipMemcpy(Fourier tables)");
+        return hip_fail(err, "hipMemcpy(Fourier tables)");
     }
     tp::FourierTables& t = fe.t;
     t.E = reinterpret_cast<const float2*>(dE);
     t.D = reinterpret_cast<const float*>(dD);
     t.cbd = reinterpret_cast<const double*>(dcbd);
     t.sbd = reinterpret_cast<const double*>(dsbd);
-    t.cb = reinterpret_cast<const float*>(dcb);
-    t.sb = reinterpret_cast<const float*>(dsb);
-    t.beta = reinterpret_cast<const float*>(dbeta);
     t.slot = reinterpret_cast<const int*>(dslot);
-    t.tile_order = reinterpret_cast<const int*>(dtile);
+    t.items = reinterpret_cast<const int4*>(ditem);
+    t.blocks = reinterpret_cast<const int4*>(dblock);
     t.na = na;
     t.n = n;
     t.N = N;
@@ -433,10 +514,9 @@ tp_status fourier_tables(const tp_plan* plan, tp_filter_kind kind, int msp, tp::
     t.M = M;
     t.log2M = ilog2(M);
     t.SL = d.SL;
-    t.nt = nt;
-    t.sw = sw;
-    t.ntiles = ntiles;
-    t.back = back;
+    t.units = units;
+    t.n_items = static_cast<int>(items.size());
+    t.n_small = static_cast<int>(small.size());
     t.s = static_cast<float>(s);
     t.inv_s = static_cast<float>(1.0 / s);
     t.msp = static_cast<float>(msp);
@@ -1375,9 +1455,11 @@ tp_status tp_fourier_fbp_chunk_out(const tp_plan* plan, const uint16_t* proj, in
                     fr_workspace(plan, n_rows, 1));
     int64_t P = static_cast<int64_t>((workspace_bytes - df) / (std::max(d.spec_pair, d.cols_pair) + d.grid_pair));
     P = std::min<int64_t>(std::max<int64_t>(P, 1), pairs);
-    const int64_t ntiles = static_cast<int64_t>(tp::fourier_grid_tiles(d.M));
-    P = std::min<int64_t>(P, 0x7fffffffLL / std::max<int64_t>({ntiles, plan->na, d.M}));
+    // work-groups of the gather per pass: at most one per 16x16 tile of half a grid and pair
+    const int64_t tiles = static_cast<int64_t>(d.M / 16) * (d.M / 32 + 2);
+    P = std::min<int64_t>(P, 0x7fffffffLL / std::max<int64_t>({tiles, plan->na + 8, d.M}));
     while (P > 1 && fr_workspace(plan, n_rows, P) > workspace_bytes) --P;
+    if (P > tp::kFrPairGroup && P < pairs) P -= P % tp::kFrPairGroup;  // whole groups of pairs in every pass
     if (P < 1) return fail(TP_EINVAL, "grid too large for one launch");
     auto st = static_cast<hipStream_t>(stream);
     tp::FourierTables t;
@@ -1387,8 +1469,8 @@ tp_status tp_fourier_fbp_chunk_out(const tp_plan* plan, const uint16_t* proj, in
     float* dmean = static_cast<float*>(workspace);
     float* den = reinterpret_cast<float*>(static_cast<char*>(workspace) + df / 2);
     char* regA = static_cast<char*>(workspace) + df;
-    char* regB = regA + align256(static_cast<size_t>(P) * std::max(d.spec_pair, d.cols_pair));
-    float2* spec = reinterpret_cast<float2*>(regA);
+    char* regB = regA + fr_region_a(d, P);
+    uint32_t* spec = reinterpret_cast<uint32_t*>(regA);
     float2* cols = reinterpret_cast<float2*>(regA);
     float2* grid = reinterpret_cast<float2*>(regB);
     tp::RawInput in{proj, proj_stride, dark, flat, frame_stride, n_dark, n_flat};

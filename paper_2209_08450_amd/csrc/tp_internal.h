@@ -55,29 +55,31 @@ struct RawInput {
 };
 
 // Tables of the Fourier-domain backprojection (one set per plan, filter
-// window and truncation radius).  Spectra rows are stored per pair of slices
-// and per angle in the order of the angles reduced modulo pi (sorted), each
-// row holding the L + 1 samples of signed frequency k = -L/2 .. L/2 at index
-// k + L/2 (reversed for angles whose reduction flipped the ray direction).
+// window and truncation radius).  Spectra rows are stored per group of four
+// pairs of slices and per angle in the order of the angles reduced modulo pi
+// (sorted), each row holding the L + 1 samples of signed frequency k = -L/2 ..
+// L/2 at index k + L/2 (reversed for angles whose reduction flipped the ray
+// direction), as two FP16 planes (the rounded sample and what it misses):
+//   spec[group][angle][plane][sample][pair of the group][re, im].
+// 2^(2 e) scales the samples into FP16's range: with counts clamped before the
+// logarithm none exceeds 2^15.
 struct FourierTables {
-    const float2* E;        // [L + 1] (pi / na) / L * w_k * H[k] * exp(2 pi i k pos0 / L)
-    const float* D;         // [N]     1 / (FT of the 1-D Gaussian at (i - N/2) / M)
+    const float2* E;        // [L + 1] 2^(2 e) (pi / na) / L * w_k * H[k] * exp(2 pi i k pos0 / L)
+    const float* D;         // [N]     2^-e / (FT of the 1-D Gaussian at (i - N/2) / M)
     const double* cbd;      // [na]    cos / sin of the sorted reduced angles, FP64
     const double* sbd;
-    const float* cb;        // [na]    the same, FP32
-    const float* sb;
-    const float* beta;      // [na]    sorted reduced angles in [0, pi), FP32
     const int* slot;        // [na]    angle a -> 2 * (sorted position) + (direction reversed)
-    const int* tile_order;  // [ntiles] 16x16 work tiles of the gather, nearest the origin first
-    int na, n, N, L, log2L, M, log2M, SL;  // SL = L + 1 samples per row
-    int nt;                 // gather taps per lane along the ray
-    int sw;                 // staged samples per (tile, angle)
-    int ntiles;
-    int back;               // staged samples before the tile centre's sample: ceil((h + 1) / s) + nt / 2
+    const int4* items;      // [n_items] work items of the gather: first point (ux, uy), first block, blocks;
+                            // n_small tiles of 16x16 points (the rest 32x32), each kind longest first
+    const int4* blocks;     // first of up to four sorted angles that reach an image of the tile, their number,
+                            // the image's centre (z, w: FP32 bits)
+    int na, n, N, L, log2L, M, log2M, SL;  // SL = L + 2 entries per row: a zero, L + 1 samples
+    int units;              // groups of 8 samples that cover a 4x4 block's reach along a ray
+    int n_items, n_small;
     float s, inv_s;         // grid points per frequency sample (M / L, a power of two >= 1)
     float msp;              // truncation radius (grid points)
     float kappa;            // log2(e) / (4 tau)
-    float ratio2;           // exp2(-2 kappa s^2): ratio of successive tap ratios
+    float ratio2;           // exp2(-2 kappa s^2): ratio of successive weights' ratios
 };
 
 // Tables of the laminographic backprojection (one set per plan, tilt, row
@@ -160,9 +162,10 @@ hipError_t launch_radon(const GeoTables& g, const float* vol, int n_rows, float*
                         hipStream_t st);
 
 hipError_t launch_fourier_spectra(const RawInput& in, int rows, const float* dmean, const float* rden,
-                                  const float2* tw_L, const FourierTables& t, float2* spec, hipStream_t st);
-size_t fourier_grid_tiles(int M);  // work-groups per pair of the gather
-hipError_t launch_fourier_grid(const FourierTables& t, const float2* spec, int pairs, float2* grid, hipStream_t st);
+                                  const float2* tw_L, const FourierTables& t, uint32_t* spec, hipStream_t st);
+// Most samples of a spectra row for one pair of slices: pairs are stored in fours.
+constexpr int kFrPairGroup = 4;
+hipError_t launch_fourier_grid(const FourierTables& t, const uint32_t* spec, int pairs, float2* grid, hipStream_t st);
 hipError_t launch_fourier_rows(const FourierTables& t, const float2* tw_M, const float2* grid, int pairs,
                                float2* cols, hipStream_t st);
 hipError_t launch_fourier_cols(const FourierTables& t, const float2* tw_M, const float2* cols, int pairs, int rows,
