@@ -213,11 +213,15 @@ __device__ __forceinline__ void reg_exchange(float2 (&x)[kRegPts], float2* lds, 
 // Forward DFT of the register-held sequence (slots: element t + B*s in, X[t + B*s] out).
 template <int L>
 __device__ __forceinline__ void reg_fft(float2 (&x)[kRegPts], float2* lds, const float2* __restrict__ tw, int t) {
-    static_assert(L >= 1024 && L <= 16384, "register FFT covers 1024..16384");
-    constexpr int log2L = (L == 1024) ? 10 : (L == 2048) ? 11 : (L == 4096) ? 12 : (L == 8192) ? 13 : 14;
+    static_assert(L >= 256 && L <= 16384, "register FFT covers 256..16384");
+    constexpr int log2L = (L == 256) ? 8 : (L == 512) ? 9 : (L == 1024) ? 10 : (L == 2048) ? 11 : (L == 4096) ? 12 : (L == 8192) ? 13 : 14;
     constexpr int rem = 1 << (log2L - 8 - ((log2L >= 12) ? 4 : 0));  // radix of the pass after the 16s
-    if constexpr (log2L < 12) {
-        // 16 x 16 x rem, rem in {4, 8}
+    if constexpr (log2L == 8) {
+        reg_pass<L, 16, false>(x, lds, 1, tw, t);
+        reg_exchange<L>(x, lds, t);
+        reg_pass<L, 16, true>(x, lds, 16, tw, t);
+    } else if constexpr (log2L < 12) {
+        // 16 x 16 x rem, rem in {2, 4, 8}
         reg_pass<L, 16, false>(x, lds, 1, tw, t);
         reg_exchange<L>(x, lds, t);
         reg_pass<L, 16, false>(x, lds, 16, tw, t);

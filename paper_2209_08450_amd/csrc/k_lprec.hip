@@ -24,11 +24,13 @@
 //                   coefficients of each row's trigonometric interpolant;
 //   k_lp_logradial  per (span, angle slot): G_k(sigma_j) from six coefficient
 //                   taps at FP64 positions, tapered, FFT over sigma;
-//   k_lp_conv       per (span, eta): the kernel column exp(...) over d, FFT,
-//                   prefilter and scale folded in (built once per launch);
-//                   per pair: FFT of the angle column, tiled M times,
-//                   multiply, inverse FFT, keep the rows of the image sector;
-//   k_lp_sigma      per (span, two rows): inverse FFT over eta, keep the rho
+//   k_lp_conv_*     per (span, eta, pair): FFT of the angle column, then per
+//                   residue r of the fine angle modulo M: multiply by the
+//                   transformed kernel taps M q + r (exp(...) over d, prefilter
+//                   and scale folded in, built once per plan), inverse FFT,
+//                   keep the rows of the image sector (columns of fewer than
+//                   256 points: one transform over all fine angles);
+//   k_lp_sigma      per (span, row): inverse FFT over eta, keep the rho
 //                   window: B-spline coefficients of F on the log-polar grid;
 //   k_lp_interp     per voxel: coordinates of every span in FP64 once, then
 //                   the 6 x 6 quintic taps of every span for every pair.
@@ -178,10 +180,10 @@ k_lp_logradial(const float2* __restrict__ rows, LprecTables t, float2* __restric
 }
 
 // ---------------------------------------------------------------------------
-// Convolution over the angle: one work-group per (span, eta), looping over the
-// pairs.  Work-groups are dealt to the 8 XCDs so that the 16 eta of one
+// Convolution over the angle for columns of fewer than 256 points (NA up to
+// 4096): one work-group per (span, eta), looping over the pairs.  Work-groups are dealt to the 8 XCDs so that the 16 eta of one
 // 128-byte line of the input run back to back on one XCD.  Output layout
-// [pair][span][m / 16][eta][16].
+// [pair][span][m / 4][eta][4].
 // ---------------------------------------------------------------------------
 template <int NA>
 __global__ void __launch_bounds__(NA / kRegPts)
@@ -234,17 +236,18 @@ k_lp_conv(const float2* __restrict__ ghat, LprecTables t, int pairs, float2* __r
         for (int s = 0; s < kRegPts; ++s) x[s] = cconj(cmul(lds[(tid + B * s) & (NAc - 1)], Kh[s]));
         __syncthreads();
         reg_fft<NA>(x, lds, t.twNA, tid);
-        float2* dst = fhat + (static_cast<int64_t>(p) * t.spans + span) * t.nmb * NS * 16;
+        float2* dst = fhat + (static_cast<int64_t>(p) * t.spans + span) * t.nqb * NS * kLpRows;
 #pragma unroll
         for (int s = 0; s < kRegPts; ++s) {
             const int m = tid + B * s - first;
             if (m >= 0 && m < t.rows)
-                dst[(static_cast<int64_t>(m >> 4) * NS + eta) * 16 + (m & 15)] = cconj(x[s]);
+                dst[(static_cast<int64_t>(m / kLpRows) * NS + eta) * kLpRows + m % kLpRows] = cconj(x[s]);
         }
     }
 }
 
-// The same convolution for NA = 8192 and 16384.  Beside a kernel column held
+// The same convolution for NA = 8192 and 16384 with NAc outside 256 .. 8192
+// (more than 32 fine angles per angle, or one).  Beside a kernel column held
 // in registers the register transform of these lengths spills, so the column
 // (transformed, prefilter and scale folded in) is built once per plan into a
 // table kt[eta][nu] (k_lp_ktable) and read per pair; the 3 spans share it.
@@ -275,10 +278,93 @@ k_lp_ktable(LprecTables t, float2* __restrict__ kt) {
     reg_fft<NA>(x, lds, t.twNA, tid);
     const float cscale = t.colscale[eta];
     float2* dst = kt + static_cast<int64_t>(eta) * NA;
+    const bool whole = !lprec_by_residue(t.NAc);
+    __syncthreads();
 #pragma unroll
     for (int s = 0; s < kRegPts; ++s) {
         const float f = t.preA[tid + B * s] * cscale;
-        dst[tid + B * s] = make_float2(x[s].x * f, x[s].y * f);
+        (whole ? dst : lds)[tid + B * s] = make_float2(x[s].x * f, x[s].y * f);
+    }
+    if (whole) return;
+    __syncthreads();
+    // residue r of output rows first + M q + r: sum over nu = l + NAc j of
+    // K[nu] exp(2 pi i nu (first + r) / NA), in FP64
+    const int NAc = t.NAc, first = t.M * (t.n_span - 1);
+    for (int o = tid; o < NA; o += B) {
+        const int l = o & (NAc - 1), r = o >> t.log2NAc;
+        double re = 0.0, im = 0.0;
+        for (int nu = l; nu < NA; nu += NAc) {
+            const float2 w = t.twNA[static_cast<int>((static_cast<int64_t>(nu) * (first + r)) & (NA - 1))], v = lds[nu];
+            re += static_cast<double>(v.x) * w.x + static_cast<double>(v.y) * w.y;
+            im += static_cast<double>(v.y) * w.x - static_cast<double>(v.x) * w.y;
+        }
+        dst[o] = make_float2(static_cast<float>(re), static_cast<float>(im));
+    }
+}
+
+// The convolution by residues: output rows first + M q + r of one r are a
+// circular convolution of the NAc-point column with every M-th tap, so one
+// forward transform serves M inverse ones of NAc points each, and none has
+// more than NAc: small work-groups, five or six to a CU, where a 16384-point
+// transform takes 16 waves in step.  One work-group per C neighbouring eta of
+// a (span, pair), 256 threads; on each XCD the 16 eta of one 128-byte line of
+// the input run for every (span, pair) in turn, so that line and the 16 kernel
+// columns come from that XCD's L2.  The result's rows lie in fours (kLpRows):
+// whole 128-byte lines for the transform over eta that reads them next cost
+// this kernel more than that one gains, and fewer lines the other way round.
+//
+// Bound: vector work (60% of the time), then the exchanges' barriers.  24
+// columns of 8192 eta, 2048 -> 16384 points: 24.5 ms as one transform of 16384
+// points per column, 8.3 ms so (512 threads for 4 eta 12.3; twiddles in
+// registers 9.0; the next kernel column fetched ahead 10.1).
+template <int NAc> constexpr int residue_columns() { return NAc < 4096 ? 4096 / NAc : 1; }
+template <int NAc> constexpr int residue_stride() { return NAc + NAc / 16 + (NAc < 1024 ? 4 : 0); }
+
+template <int NAc>
+__global__ void __launch_bounds__(residue_columns<NAc>() * NAc / kRegPts, 3)
+k_lp_conv_residue(const float2* __restrict__ ghat, LprecTables t, int pairs, float2* __restrict__ fhat) {
+    extern __shared__ float2 lds[];
+    constexpr int B = NAc / kRegPts, C = residue_columns<NAc>(), T = C * B;
+    const int tid = threadIdx.x % B, c = threadIdx.x / B;
+    const int NS = t.Ns;
+    const int id = blockIdx.x;
+    const int xcd = id & 7, rr = id >> 3;
+    const int per = t.spans * pairs * (16 / C);  // work-groups per 16-eta group on one XCD
+    const int G = rr / per, rem = rr - G * per;
+    const int sp = rem / (16 / C);
+    const int span = sp / pairs, p = sp - span * pairs;
+    const int eta0 = (G * 8 + xcd) * 16 + rem % (16 / C) * C, eta = eta0 + c;
+    const float2* src = ghat + ((static_cast<int64_t>(p) * t.spans + span) * (NS / 16) + (eta0 >> 4)) *
+                                   t.n_span * 16 + (eta0 & 15);
+    for (int i = threadIdx.x; i < C * t.n_span; i += T)
+        lds[i % C * residue_stride<NAc>() + i / C] = src[static_cast<int64_t>(i / C) * 16 + i % C];
+    __syncthreads();
+    float2* mine = lds + c * residue_stride<NAc>();
+    float2 X[kRegPts];
+#pragma unroll
+    for (int s = 0; s < kRegPts; ++s)
+        X[s] = tid + B * s < t.n_span ? mine[tid + B * s] : make_float2(0.0f, 0.0f);
+    __syncthreads();
+    reg_fft<NAc>(X, mine, t.twNAc, tid);
+    const float2* kcol = t.kt + static_cast<int64_t>(eta) * t.NA;
+    float2* dst = fhat + (static_cast<int64_t>(p) * t.spans + span) * t.residues * t.nqb * NS * kLpRows + eta * kLpRows;
+#pragma unroll 1
+    for (int r = 0; r < t.residues; ++r) {
+        // an opaque thread index per residue keeps twiddles and offsets from
+        // being hoisted into registers held across the loop
+        int ti = tid;
+        asm volatile("" : "+v"(ti));
+        float2 x[kRegPts];
+#pragma unroll
+        for (int s = 0; s < kRegPts; ++s) x[s] = cconj(cmul(X[s], kcol[ti + B * s]));
+        kcol += NAc;
+        reg_fft<NAc>(x, mine, t.twNAc, ti);
+#pragma unroll
+        for (int s = 0; s < kRegPts; ++s) {
+            const int q = ti + B * s;
+            if (q * t.residues + r < t.rows) dst[static_cast<int64_t>(q / kLpRows) * NS * kLpRows + q % kLpRows] = cconj(x[s]);
+        }
+        dst += static_cast<int64_t>(t.nqb) * NS * kLpRows;
     }
 }
 
@@ -315,54 +401,49 @@ k_lp_conv_tab(const float2* __restrict__ ghat, LprecTables t, int pairs, float2*
     for (int s = 0; s < kRegPts; ++s) x[s] = cconj(cmul(lds[(tid + B * s) & (NAc - 1)], kcol[tid + B * s]));
     __syncthreads();
     reg_fft<NA>(x, lds, t.twNA, tid);
-    float2* dst = fhat + (static_cast<int64_t>(p) * t.spans + span) * t.nmb * NS * 16;
+    float2* dst = fhat + (static_cast<int64_t>(p) * t.spans + span) * t.nqb * NS * kLpRows;
 #pragma unroll
     for (int s = 0; s < kRegPts; ++s) {
         const int m = tid + B * s - first;
-        if (m >= 0 && m < t.rows) dst[(static_cast<int64_t>(m >> 4) * NS + eta) * 16 + (m & 15)] = cconj(x[s]);
+        if (m >= 0 && m < t.rows) dst[(static_cast<int64_t>(m / kLpRows) * NS + eta) * kLpRows + m % kLpRows] = cconj(x[s]);
     }
 }
 
 // ---------------------------------------------------------------------------
-// Inverse transform over sigma: one work-group per (pair, span, two rows);
-// the 8 work-groups of one 16-row line group run back to back on one XCD.
-// Output F [pair][span][row][nj] (the rho window).
+// Inverse transform over sigma: one work-group per (pair, span, row); the
+// four rows that share their lines run back to back on one XCD.  Output F
+// [pair][span][row][nj] (the rho window).  Bound: memory (7.4 GB read, 2.7
+// written for 24 x 4720 rows of 8192 points: 4.9 ms; two rows of a group of 16
+// per work-group, 184 registers and one work-group to a CU: 7.8 ms).
 // ---------------------------------------------------------------------------
 template <int NS>
-__global__ void __launch_bounds__(NS / kRegPts)
+__global__ void __launch_bounds__(NS / kRegPts, 4)
 k_lp_sigma(const float2* __restrict__ fhat, LprecTables t, int pairs, float2* __restrict__ F) {
     extern __shared__ float2 lds[];
     constexpr int B = NS / kRegPts;
     const int tid = threadIdx.x;
     const int id = blockIdx.x;
     const int xcd = id & 7, r = id >> 3;
-    const int r2 = r & 7;
-    const int64_t gidx = static_cast<int64_t>(r >> 3) * 8 + xcd;
-    const int64_t G = static_cast<int64_t>(pairs) * t.spans * t.nmb;
+    const int r2 = r % kLpRows;
+    const int64_t gidx = static_cast<int64_t>(r / kLpRows) * 8 + xcd;
+    const int64_t G = static_cast<int64_t>(pairs) * t.spans * t.residues * t.nqb;
     if (gidx >= G) return;  // whole work-group
-    const int mb = static_cast<int>(gidx % t.nmb);
-    const int64_t ps = gidx / t.nmb;  // pair * spans + span
-    const int m = mb * 16 + 2 * r2;
+    const int64_t psr = gidx / t.nqb;  // (pair * spans + span) * residues + residue
+    const int64_t ps = psr / t.residues;
+    const int q = static_cast<int>(gidx - psr * t.nqb) * kLpRows + r2;
+    const int m = q * t.residues + static_cast<int>(psr - ps * t.residues);
     if (m >= t.rows) return;
-    const float4* src = reinterpret_cast<const float4*>(fhat + (ps * t.nmb + mb) * NS * 16 + (m & 15));
-    float2 x[kRegPts], y[kRegPts];
+    const float2* src = fhat + gidx * NS * kLpRows + r2;
+    float2 x[kRegPts];
+#pragma unroll
+    for (int s = 0; s < kRegPts; ++s) x[s] = cconj(src[static_cast<int64_t>(tid + B * s) * kLpRows]);
+    reg_fft<NS>(x, lds, t.twNs, tid);
+    float2* dst = F + (ps * t.rows + m) * t.nj;
 #pragma unroll
     for (int s = 0; s < kRegPts; ++s) {
-        const float4 v = src[static_cast<int64_t>(tid + B * s) * 8];
-        x[s] = make_float2(v.x, 0.0f - v.y);
-        y[s] = make_float2(v.z, 0.0f - v.w);
+        const int j = tid + B * s - t.j_lo;
+        if (j >= 0 && j < t.nj) dst[j] = cconj(x[s]);
     }
-    auto finish = [&](float2 (&v)[kRegPts], int row) {
-        reg_fft<NS>(v, lds, t.twNs, tid);
-        float2* dst = F + (ps * t.rows + row) * t.nj;
-#pragma unroll
-        for (int s = 0; s < kRegPts; ++s) {
-            const int j = tid + B * s - t.j_lo;
-            if (j >= 0 && j < t.nj) dst[j] = cconj(v[s]);
-        }
-    };
-    finish(x, m);
-    if (m + 1 < t.rows) finish(y, m + 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -453,18 +534,29 @@ hipError_t launch_conv_t(const LprecTables& t, const float2* ghat, int pairs, fl
 
 template <int NA>
 hipError_t launch_ktable_t(const LprecTables& t, float2* kt, hipStream_t st) {
-    if constexpr (NA >= 8192) {
-        hipLaunchKernelGGL(k_lp_ktable<NA>, dim3(t.Ns), dim3(NA / kRegPts), reg_lds_bytes(NA), st, t, kt);
-        return hipGetLastError();
-    } else {
-        return hipSuccess;
-    }
+    hipLaunchKernelGGL(k_lp_ktable<NA>, dim3(t.Ns), dim3(NA / kRegPts), reg_lds_bytes(NA), st, t, kt);
+    return hipGetLastError();
+}
+
+template <int NAc>
+size_t residue_lds() {
+    return static_cast<size_t>(residue_columns<NAc>()) * residue_stride<NAc>() * sizeof(float2);
+}
+
+template <int NAc>
+hipError_t launch_residue_t(const LprecTables& t, const float2* ghat, int pairs, float2* fhat, hipStream_t st) {
+    // the eta-group order needs Ns / 16 divisible by 8
+    const int64_t blocks = static_cast<int64_t>(t.spans) * t.Ns * pairs / residue_columns<NAc>();
+    if (blocks > 0x7fffffff || (t.Ns / 16) % 8 != 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_lp_conv_residue<NAc>, dim3(static_cast<unsigned>(blocks)),
+                       dim3(residue_columns<NAc>() * NAc / kRegPts), residue_lds<NAc>(), st, ghat, t, pairs, fhat);
+    return hipGetLastError();
 }
 
 template <int NS>
 hipError_t launch_sigma_t(const LprecTables& t, const float2* fhat, int pairs, float2* F, hipStream_t st) {
-    const int64_t G = static_cast<int64_t>(pairs) * t.spans * t.nmb;
-    const int64_t blocks = ((G + 7) / 8) * 64;
+    const int64_t G = static_cast<int64_t>(pairs) * t.spans * t.residues * t.nqb;
+    const int64_t blocks = (G + 7) / 8 * 8 * kLpRows;
     hipLaunchKernelGGL(k_lp_sigma<NS>, dim3(static_cast<unsigned>(blocks)), dim3(NS / kRegPts), reg_lds_bytes(NS),
                        st, fhat, t, pairs, F);
     return hipGetLastError();
@@ -480,6 +572,17 @@ hipError_t launch_sigma_t(const LprecTables& t, const float2* fhat, int pairs, f
         default: return hipErrorInvalidValue;             \
     }
 
+#define TP_LP_RESIDUE(len, fn, ...)                       \
+    switch (len) {                                        \
+        case 256: return fn<256>(__VA_ARGS__);            \
+        case 512: return fn<512>(__VA_ARGS__);            \
+        case 1024: return fn<1024>(__VA_ARGS__);          \
+        case 2048: return fn<2048>(__VA_ARGS__);          \
+        case 4096: return fn<4096>(__VA_ARGS__);          \
+        case 8192: return fn<8192>(__VA_ARGS__);          \
+        default: return hipErrorInvalidValue;             \
+    }
+
 template <int NS>
 hipError_t prep_ns(const LprecTables& t) {
     hipError_t e = lds_limit(k_lp_logradial<NS>, std::max(reg_lds_bytes(NS), static_cast<size_t>(2 * t.L) * 8));
@@ -489,13 +592,18 @@ hipError_t prep_ns(const LprecTables& t) {
 
 template <int NA>
 hipError_t prep_na(const LprecTables& t) {
+    const hipError_t e = lds_limit(k_lp_ktable<NA>, reg_lds_bytes(NA));
+    if (e != hipSuccess || lprec_by_residue(t.NAc)) return e;
     if constexpr (NA >= 8192) {
-        hipError_t e = lds_limit(k_lp_ktable<NA>, reg_lds_bytes(NA));
-        if (e != hipSuccess) return e;
         return lds_limit(k_lp_conv_tab<NA>, conv_lds_bytes(NA, t.NAc));
     } else {
         return lds_limit(k_lp_conv<NA>, conv_lds_bytes(NA, t.NAc));
     }
+}
+
+template <int NAc>
+hipError_t prep_residue() {
+    return lds_limit(k_lp_conv_residue<NAc>, residue_lds<NAc>());
 }
 
 }  // namespace
@@ -505,7 +613,9 @@ hipError_t prepare_lprec(const LprecTables& t) {
     if (e != hipSuccess) return e;
     e = [&]() -> hipError_t { TP_LP_DISPATCH(t.Ns, prep_ns, t) }();
     if (e != hipSuccess) return e;
-    TP_LP_DISPATCH(t.NA, prep_na, t)
+    e = [&]() -> hipError_t { TP_LP_DISPATCH(t.NA, prep_na, t) }();
+    if (e != hipSuccess || !lprec_by_residue(t.NAc)) return e;
+    TP_LP_RESIDUE(t.NAc, prep_residue)
 }
 
 hipError_t launch_lprec_rows(const RawInput& in, int rows, const float* dmean, const float* rden,
@@ -522,11 +632,12 @@ hipError_t launch_lprec_logradial(const LprecTables& t, const float2* rows, int 
 }
 
 hipError_t launch_lprec_conv(const LprecTables& t, const float2* ghat, int pairs, float2* fhat, hipStream_t st) {
+    if (lprec_by_residue(t.NAc)) { TP_LP_RESIDUE(t.NAc, launch_residue_t, t, ghat, pairs, fhat, st) }
     TP_LP_DISPATCH(t.NA, launch_conv_t, t, ghat, pairs, fhat, st)
 }
 
-size_t lprec_ktable_bytes(int Ns, int NA) {
-    return NA >= 8192 ? static_cast<size_t>(Ns) * NA * sizeof(float2) : 0;
+size_t lprec_ktable_bytes(int Ns, int NA, int NAc) {
+    return NA >= 8192 || lprec_by_residue(NAc) ? static_cast<size_t>(Ns) * NA * sizeof(float2) : 0;
 }
 
 hipError_t launch_lprec_ktable(const LprecTables& t, float2* kt, hipStream_t st) {

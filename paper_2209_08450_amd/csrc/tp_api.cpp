@@ -717,11 +717,12 @@ struct LpSizes {
 
 LpSizes lp_sizes(const tp_plan* plan, const tp_lprec_grid& g) {
     const int L = plan->filt.L;
-    const size_t nmb = static_cast<size_t>((g.rows + 15) / 16);
+    const int residues = tp::lprec_by_residue(g.NA / g.M) ? g.M : 1;
+    const size_t groups = static_cast<size_t>(residues) * (((g.rows + residues - 1) / residues + tp::kLpRows - 1) / tp::kLpRows);
     LpSizes z;
     z.rows = sizeof(float2) * static_cast<size_t>(plan->na) * 2 * L;
     z.ghat = sizeof(float2) * static_cast<size_t>(g.spans) * g.Ns * g.n_span;
-    z.fhat = sizeof(float2) * static_cast<size_t>(g.spans) * nmb * g.Ns * 16;
+    z.fhat = sizeof(float2) * static_cast<size_t>(g.spans) * groups * g.Ns * tp::kLpRows;
     z.F = sizeof(float2) * static_cast<size_t>(g.spans) * g.rows * g.nj;
     return z;
 }
@@ -800,7 +801,7 @@ tp_status lprec_tables(const tp_plan* plan, tp_filter_kind kind, const tp_lprec_
                                {twNA.data(), sizeof(float2) * NA, nullptr},     {twNAc.data(), sizeof(float2) * NAc, nullptr}};
     size_t total = 0;
     for (const Part& q : parts) total += align256(q.bytes);
-    const size_t kt_bytes = tp::lprec_ktable_bytes(Ns, NA);
+    const size_t kt_bytes = tp::lprec_ktable_bytes(Ns, NA, NAc);
     total += align256(kt_bytes);
     LprecEntry le;
     hipError_t e = hipMalloc(&le.block, total);
@@ -845,7 +846,8 @@ tp_status lprec_tables(const tp_plan* plan, tp_filter_kind kind, const tp_lprec_
     t.log2NAc = ilog2(NAc);
     t.D = g.D;
     t.rows = g.rows;
-    t.nmb = (g.rows + 15) / 16;
+    t.residues = tp::lprec_by_residue(NAc) ? g.M : 1;
+    t.nqb = ((g.rows + t.residues - 1) / t.residues + tp::kLpRows - 1) / tp::kLpRows;
     t.m_lo = g.m_lo;
     t.j_lo = g.j_lo;
     t.nj = g.nj;

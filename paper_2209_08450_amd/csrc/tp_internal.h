@@ -107,6 +107,11 @@ struct LaminoTables {
 // Grids: sigma_j = sigma0 + j delta (j < Ns), psi_m = phi0 + m dpsi,
 // dpsi = dtheta / M, stored rows m_lo .. m_lo + rows - 1, stored sigma
 // window j_lo .. j_lo + nj - 1.
+// The angle convolution by residues of the output row modulo M (one transform
+// of NAc points each); shorter columns take one transform of NA = M NAc points.
+constexpr bool lprec_by_residue(int NAc) { return NAc >= 256 && NAc <= 8192; }
+constexpr int kLpRows = 4;  // rows side by side in the convolution's result
+
 struct LprecTables {
     const float* T0;        // [L]   H[k] / (L B(k~ / 2L)): row spline multiplier, even half-samples
     const float2* T1;       // [L]   T0[k] exp(i pi k~ / L), zero at L/2: odd half-samples
@@ -122,8 +127,10 @@ struct LprecTables {
     const float2* twNs;     // [Ns]
     const float2* twNA;     // [NA]
     const float2* twNAc;    // [NAc]
-    const float2* kt;       // [Ns][NA] transformed kernel columns, prefilter and scale folded in (NA >= 8192)
-    int na, n, N, L, log2L, spans, n_span, Ns, NA, M, NAc, log2NAc, D, rows, nmb, m_lo, j_lo, nj;
+    const float2* kt;       // [Ns][NA] transformed kernel columns, prefilter and scale folded in: by residue (by_residue) or whole
+    int na, n, N, L, log2L, spans, n_span, Ns, NA, M, NAc, log2NAc, D, rows, m_lo, j_lo, nj;
+    int residues;           // fhat holds row m as row m / residues of residue m % residues
+    int nqb;                // groups of kLpRows such rows
     double a0, sigma0, delta, phi0, dpsi;
 };
 
@@ -185,7 +192,7 @@ hipError_t launch_lprec_interp(const LprecTables& t, const float2* F, int pairs,
 hipError_t prepare_lprec(const LprecTables& t);
 // The transformed kernel table of the long angle transforms: its size (0 when
 // the convolution holds the columns in registers) and the launch that fills it.
-size_t lprec_ktable_bytes(int Ns, int NA);
+size_t lprec_ktable_bytes(int Ns, int NA, int NAc);
 hipError_t launch_lprec_ktable(const LprecTables& t, float2* kt, hipStream_t st);
 
 // measurement instruments (k_peak.hip)
