@@ -179,8 +179,11 @@ constexpr int kPairsPerGroup = 8;
 // and 12-15 right padding at compile time: padding slots load nothing and
 // hold no registers.  Otherwise the same tests run on the runtime offsets
 // (each is uniform over the work-group).
+// 4096 points: held to 168 registers, three work-groups of 4 waves to a CU (170
+// and two: 2.13 ms for 128 rows of 2048 angles x 2048 columns, three 1.86; the
+// other lengths fit as they are).
 template <int L, int ST, bool HALF>
-__global__ void __launch_bounds__(L / kRegPts)
+__global__ void __launch_bounds__(L / kRegPts, L == 4096 ? 3 : 1)
 k_norm_filter_reg(RawInput in, const float* __restrict__ dmean, const float* __restrict__ rden, int n_angles, int n_rows,
                   int n, int off, FilterTables ft, uint16_t* out) {
     extern __shared__ float2 lds[];

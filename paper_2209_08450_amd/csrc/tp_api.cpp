@@ -195,6 +195,23 @@ void filter_response_fp64(int L, tp_filter_kind kind, std::vector<double>& H) {
 
 bool valid_kind(tp_filter_kind k) { return k == TP_RAMP || k == TP_SHEPP || k == TP_PARZEN; }
 
+// exp(-2 pi i k / L), k < L, then the same values in the order in which the
+// passes of the register transform read them: the pass of radix R behind passes
+// of product Ns takes exp(-2 pi i k r / (R Ns)) from entry L + Ns r + k.
+std::vector<float2> fft_twiddles(int L) {
+    std::vector<float2> tw(2 * static_cast<size_t>(L), make_float2(0.0f, 0.0f));
+    for (int k = 0; k < L; ++k) {
+        const double ang = -2.0 * M_PI * static_cast<double>(k) / L;
+        tw[k] = make_float2(static_cast<float>(std::cos(ang)), static_cast<float>(std::sin(ang)));
+    }
+    for (int Ns = 1, R; Ns < L; Ns *= R) {
+        R = std::min(16, L / Ns);
+        for (int r = 1; r < R; ++r)
+            for (int k = 0; k < Ns; ++k) tw[static_cast<size_t>(L) + Ns * r + k] = tw[k * r * (L / (Ns * R))];
+    }
+    return tw;
+}
+
 tp_status filter_tables(int L, tp_filter_kind kind, tp::FilterTables* out, hipStream_t st_for_capture_check) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -213,22 +230,18 @@ tp_status filter_tables(int L, tp_filter_kind kind, tp::FilterTables* out, hipSt
         }
         std::vector<double> H;
         filter_response_fp64(L, kind, H);
-        std::vector<float2> tw(L);
+        const std::vector<float2> tw = fft_twiddles(L);
         std::vector<float> hf(L);
-        for (int k = 0; k < L; ++k) {
-            const double ang = -2.0 * M_PI * static_cast<double>(k) / L;
-            tw[k] = make_float2(static_cast<float>(std::cos(ang)), static_cast<float>(std::sin(ang)));
-            hf[k] = static_cast<float>(H[k] / L);
-        }
+        for (int k = 0; k < L; ++k) hf[k] = static_cast<float>(H[k] / L);
         FilterEntry fe;
-        e = hipMalloc(&fe.tw, sizeof(float2) * L);
+        e = hipMalloc(&fe.tw, sizeof(float2) * tw.size());
         if (e != hipSuccess) return fail(TP_ENOMEM, "hipMalloc(filter twiddles): %s", hipGetErrorString(e));
         e = hipMalloc(&fe.H, sizeof(float) * L);
         if (e != hipSuccess) {
             (void)hipFree(fe.tw);
             return fail(TP_ENOMEM, "hipMalloc(filter response): %s", hipGetErrorString(e));
         }
-        e = hipMemcpy(fe.tw, tw.data(), sizeof(float2) * L, hipMemcpyHostToDevice);
+        e = hipMemcpy(fe.tw, tw.data(), sizeof(float2) * tw.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(fe.H, hf.data(), sizeof(float) * L, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             (void)hipFree(fe.tw);
@@ -778,15 +791,8 @@ tp_status lprec_tables(const tp_plan* plan, tp_filter_kind kind, const tp_lprec_
         cbp[p] = std::cos(beta);
         sbp[p] = std::sin(beta);
     }
-    auto twiddles = [](int len) {
-        std::vector<float2> tw(len);
-        for (int k = 0; k < len; ++k) {
-            const double ang = -2.0 * M_PI * static_cast<double>(k) / len;
-            tw[k] = make_float2(static_cast<float>(std::cos(ang)), static_cast<float>(std::sin(ang)));
-        }
-        return tw;
-    };
-    const std::vector<float2> twL = twiddles(L), twNs = twiddles(Ns), twNA = twiddles(NA), twNAc = twiddles(NAc);
+    const std::vector<float2> twL = fft_twiddles(L), twNs = fft_twiddles(Ns), twNA = fft_twiddles(NA),
+                              twNAc = fft_twiddles(NAc);
     struct Part {
         const void* src;
         size_t bytes;
@@ -797,8 +803,8 @@ tp_status lprec_tables(const tp_plan* plan, tp_filter_kind kind, const tp_lprec_
                                {A.data(), sizeof(double) * g.n_span, nullptr},  {cd.data(), sizeof(double) * g.D, nullptr},
                                {preA.data(), sizeof(float) * NA, nullptr},      {colscale.data(), sizeof(float) * Ns, nullptr},
                                {cbp.data(), sizeof(double) * g.spans, nullptr}, {sbp.data(), sizeof(double) * g.spans, nullptr},
-                               {twL.data(), sizeof(float2) * L, nullptr},       {twNs.data(), sizeof(float2) * Ns, nullptr},
-                               {twNA.data(), sizeof(float2) * NA, nullptr},     {twNAc.data(), sizeof(float2) * NAc, nullptr}};
+                               {twL.data(), sizeof(float2) * 2 * L, nullptr},   {twNs.data(), sizeof(float2) * 2 * Ns, nullptr},
+                               {twNA.data(), sizeof(float2) * 2 * NA, nullptr}, {twNAc.data(), sizeof(float2) * 2 * NAc, nullptr}};
     size_t total = 0;
     for (const Part& q : parts) total += align256(q.bytes);
     const size_t kt_bytes = tp::lprec_ktable_bytes(Ns, NA, NAc);

@@ -39,7 +39,7 @@ struct GeoTables {
 };
 
 struct FilterTables {
-    const float2* tw;  // [L]  exp(-2 pi i k / L)
+    const float2* tw;  // [2 L] exp(-2 pi i k / L), then the same in the register transform's order (fft_device.h)
     const float* H;    // [L]  H[k] / L (ramp response, inverse-FFT scale folded in)
     int L, log2L;
 };
@@ -123,10 +123,10 @@ struct LprecTables {
     const float* colscale;  // [Ns]  dtheta / (NA Ns B(eta / Ns))
     const double* cb;       // [spans] cos(beta_p), FP64
     const double* sb;       // [spans] sin(beta_p)
-    const float2* twL;      // [L]   exp(-2 pi i k / L)
-    const float2* twNs;     // [Ns]
-    const float2* twNA;     // [NA]
-    const float2* twNAc;    // [NAc]
+    const float2* twL;      // [2 L] exp(-2 pi i k / L), then in the register transform's order
+    const float2* twNs;     // [2 Ns]
+    const float2* twNA;     // [2 NA]
+    const float2* twNAc;    // [2 NAc]
     const float2* kt;       // [Ns][NA] transformed kernel columns, prefilter and scale folded in: by residue (by_residue) or whole
     int na, n, N, L, log2L, spans, n_span, Ns, NA, M, NAc, log2NAc, D, rows, m_lo, j_lo, nj;
     int residues;           // fhat holds row m as row m / residues of residue m % residues
