@@ -77,7 +77,8 @@ size_t reg_lds_bytes(int L) { return static_cast<size_t>(L + L / 16) * sizeof(fl
 int rows_block(int L) { return L / 16 < 64 ? 64 : (L / 16 > 1024 ? 1024 : L / 16); }
 
 // ---------------------------------------------------------------------------
-// Row splines: one work-group per (angle, pair of slices).
+// Row splines: one work-group per (angle, pair of slices); rows of fewer than
+// 1024 points through LDS.
 // ---------------------------------------------------------------------------
 constexpr int kRowSlots = 16;  // L / blockDim elements per thread (blockDim >= L / 16)
 
@@ -122,6 +123,47 @@ k_lp_rows(RawInput in, int rows, const float* __restrict__ dmean, const float* _
         fft_forward_lds(buf, L, t.log2L, t.twL);
         for (int i = tid; i < L; i += B) dst[2 * i + b] = cconj(buf[i]);
     }
+}
+
+// The same for 1024 <= L <= 8192 with the register transform: both inverse
+// transforms' results meet in registers and are stored as whole lines.  Bound:
+// three transforms per row (16 rows of 2048 angles, L = 4096: 1.93 ms through
+// LDS, 0.58 so; 4096 points are held to 168 registers, three work-groups to a CU).
+template <int L>
+__global__ void __launch_bounds__(L / kRegPts, L == 4096 ? 3 : 1)
+k_lp_rows_reg(RawInput in, int rows, const float* __restrict__ dmean, const float* __restrict__ rden, LprecTables t,
+              float2* __restrict__ out) {
+    extern __shared__ float2 lds[];
+    constexpr int B = L / kRegPts;
+    const int a = blockIdx.x, p = blockIdx.y;
+    const int n = t.n, off = (L - n) / 2, tid = threadIdx.x;
+    const int z0 = 2 * p;
+    const bool has1 = z0 + 1 < rows;
+    const int64_t r0 = static_cast<int64_t>(z0) * n;
+    const int64_t r1 = has1 ? r0 + n : r0;
+    const uint16_t* q0 = in.proj + a * in.proj_stride + r0;
+    const uint16_t* q1 = in.proj + a * in.proj_stride + r1;
+    float2 X[kRegPts];
+#pragma unroll
+    for (int s = 0; s < kRegPts; ++s) {
+        const int c = min(max(tid + B * s - off, 0), n - 1);
+        X[s] = make_float2(neglog_counts(static_cast<float>(q0[c]), dmean[r0 + c], rden[r0 + c]),
+                           has1 ? neglog_counts(static_cast<float>(q1[c]), dmean[r1 + c], rden[r1 + c]) : 0.0f);
+    }
+    reg_fft<L>(X, lds, t.twL, tid);
+    float2 e[kRegPts];
+#pragma unroll
+    for (int s = 0; s < kRegPts; ++s) {
+        const float h = t.T0[tid + B * s];
+        e[s] = make_float2(X[s].x * h, 0.0f - X[s].y * h);
+        X[s] = cconj(cmul(X[s], t.T1[tid + B * s]));
+    }
+    reg_fft<L>(e, lds, t.twL, tid);
+    reg_fft<L>(X, lds, t.twL, tid);
+    float4* dst = reinterpret_cast<float4*>(out + (static_cast<int64_t>(p) * t.na + a) * (2 * L));
+#pragma unroll
+    for (int s = 0; s < kRegPts; ++s)
+        dst[tid + B * s] = make_float4(e[s].x, 0.0f - e[s].y, X[s].x, 0.0f - X[s].y);
 }
 
 // ---------------------------------------------------------------------------
@@ -602,6 +644,14 @@ hipError_t prep_na(const LprecTables& t) {
     }
 }
 
+template <int L>
+hipError_t launch_rows_reg(const RawInput& in, int rows, const float* dmean, const float* rden, const LprecTables& t,
+                           float2* out, hipStream_t st) {
+    hipLaunchKernelGGL(k_lp_rows_reg<L>, dim3(t.na, (rows + 1) / 2), dim3(L / kRegPts), reg_lds_bytes(L), st, in, rows,
+                       dmean, rden, t, out);
+    return hipGetLastError();
+}
+
 template <int NAc>
 hipError_t prep_residue() {
     return lds_limit(k_lp_conv_residue<NAc>, residue_lds<NAc>());
@@ -610,7 +660,9 @@ hipError_t prep_residue() {
 }  // namespace
 
 hipError_t prepare_lprec(const LprecTables& t) {
-    hipError_t e = lds_limit(k_lp_rows, static_cast<size_t>(t.L) * sizeof(float2));
+    hipError_t e = t.L == 8192 ? lds_limit(k_lp_rows_reg<8192>, reg_lds_bytes(8192)) : hipSuccess;
+    if (e != hipSuccess) return e;
+    e = lds_limit(k_lp_rows, static_cast<size_t>(t.L) * sizeof(float2));
     if (e != hipSuccess) return e;
     e = [&]() -> hipError_t { TP_LP_DISPATCH(t.Ns, prep_ns, t) }();
     if (e != hipSuccess) return e;
@@ -622,6 +674,13 @@ hipError_t prepare_lprec(const LprecTables& t) {
 hipError_t launch_lprec_rows(const RawInput& in, int rows, const float* dmean, const float* rden,
                              const LprecTables& t, float2* out, hipStream_t st) {
     const int pairs = (rows + 1) / 2;
+    switch (t.L) {
+        case 1024: return launch_rows_reg<1024>(in, rows, dmean, rden, t, out, st);
+        case 2048: return launch_rows_reg<2048>(in, rows, dmean, rden, t, out, st);
+        case 4096: return launch_rows_reg<4096>(in, rows, dmean, rden, t, out, st);
+        case 8192: return launch_rows_reg<8192>(in, rows, dmean, rden, t, out, st);
+        default: break;
+    }
     hipLaunchKernelGGL(k_lp_rows, dim3(t.na, pairs), dim3(rows_block(t.L)), static_cast<size_t>(t.L) * sizeof(float2),
                        st, in, rows, dmean, rden, t, out);
     return hipGetLastError();

@@ -52,3 +52,19 @@ def test_residue_convolution_matches_oracle(tp, case):
     torch.cuda.synchronize()
     want = olp.lprec_fbp(s.proj, s.dark, s.flat, 0.2, s.center, spans=spans, os=os_)
     assert_parity(to_host(out).astype(np.float64), want, "f32", label=f"lprec residue {case}")
+
+
+# detector -> points of a padded row: through LDS below 1024, in registers from
+# there; an axis near the detector's edge and an odd last pair
+@pytest.mark.parametrize("n,points", [(255, 512), (257, 1024), (512, 1024), (513, 2048), (1500, 4096), (2100, 8192)])
+def test_row_splines_match_oracle(tp, n, points):
+    import torch
+    na, rows, N = 90, 3, 40
+    s = synth.ellipsoid_scan_np(seed=n, n_angles=na, n_rows=rows, n_det=n, center=0.5 * n + 2.7, n_dark=2, n_flat=2,
+                                n_ellipsoids=8)
+    plan = tp.Plan(np.arange(na) * math.pi / na, n, s.center, N)
+    note(f"lprec row splines {n} columns, {points} points")
+    out = tp.lprec_fbp_chunk(plan, to_dev(s.proj), to_dev(s.dark), to_dev(s.flat))
+    torch.cuda.synchronize()
+    want = olp.lprec_fbp(s.proj, s.dark, s.flat, 0.0, s.center, N)
+    assert_parity(to_host(out).astype(np.float64), want, "f32", label=f"lprec row splines {n}")
