@@ -174,6 +174,19 @@ template <int R> struct Dft {
 
 constexpr int kRegPts = 16;
 
+// Transforms that a work-group takes one after the other, each one's input
+// loaded while the one before is transformed: 8 where that leaves work-groups
+// for the whole chip, fewer on small inputs (one row of 900 angles x 1024
+// columns, 64 work-groups of 8 pairs: 52 us, 450 of one: 19 us; 5 pairs of rows
+// of 721 angles, 455 of 8: 97 us, 3605 of one: 62 us; 1024 or 4096 in place of
+// 2048 make no difference).
+constexpr int kMaxRun = 8, kFullGroups = 2048;
+inline int run_length(int64_t rows, int transforms) {
+    int run = kMaxRun;
+    while (run > 1 && rows * ((transforms + run - 1) / run) < kFullGroups) run /= 2;
+    return run;
+}
+
 __device__ __forceinline__ int lds_pad(int i) { return i + (i >> 4); }
 
 // One Stockham pass of radix R over the 16 register slots; Ns = product of

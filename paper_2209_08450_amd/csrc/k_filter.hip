@@ -170,10 +170,9 @@ k_filter_reg(const TI* in, TO* out, int64_t n_lines, int n, int off, FilterTable
 }
 
 
-// Angle pairs per work-group of the fused kernel: each pair's raw counts are
+// A work-group takes `run` angle pairs (run_length): each pair's raw counts are
 // prefetched into registers while the previous pair is transformed.
-constexpr int kPairsPerGroup = 8;
-
+//
 // HALF: the detector fills the middle half of the padded row (n = L/2, off =
 // L/4, every power-of-two detector), so slots 0-3 are left padding, 4-11 data
 // and 12-15 right padding at compile time: padding slots load nothing and
@@ -185,16 +184,16 @@ constexpr int kPairsPerGroup = 8;
 template <int L, int ST, bool HALF>
 __global__ void __launch_bounds__(L / kRegPts, L == 4096 ? 3 : 1)
 k_norm_filter_reg(RawInput in, const float* __restrict__ dmean, const float* __restrict__ rden, int n_angles, int n_rows,
-                  int n, int off, FilterTables ft, uint16_t* out) {
+                  int n, int off, int run, FilterTables ft, uint16_t* out) {
     extern __shared__ float2 lds[];
     constexpr int B = L / kRegPts;
     const int pairs = (n_angles + 1) >> 1;
-    const int groups = (pairs + kPairsPerGroup - 1) / kPairsPerGroup;
+    const int groups = (pairs + run - 1) / run;
     int r, g0;
     blocked_work(n_rows, groups, r, g0);
     if (r >= n_rows) return;  // whole work-group
-    g0 *= kPairsPerGroup;
-    const int g1 = min(pairs, g0 + kPairsPerGroup);
+    g0 *= run;
+    const int g1 = min(pairs, g0 + run);
     const float* dm = dmean + static_cast<int64_t>(r) * n;
     const float* dn = rden + static_cast<int64_t>(r) * n;
     // the thread's FFT twiddles, the same for every transform of the group
@@ -349,7 +348,8 @@ hipError_t launch_norm_filter_t(const RawInput& in, const float* dmean, const fl
     const int off = (ft.L - n) / 2;
     const int pairs = (n_angles + 1) / 2;
     const dim3 grid(blocked_grid(n_rows, pairs));
-    const dim3 reg_grid(blocked_grid(n_rows, (pairs + kPairsPerGroup - 1) / kPairsPerGroup));
+    const int run = run_length(n_rows, pairs);
+    const dim3 reg_grid(blocked_grid(n_rows, (pairs + run - 1) / run));
     uint16_t* pout = static_cast<uint16_t*>(out);
     size_t lds = 0;
     hipError_t e = hipSuccess;
@@ -359,12 +359,12 @@ hipError_t launch_norm_filter_t(const RawInput& in, const float* dmean, const fl
             e = launch_reg<LL>(k_norm_filter_reg<LL, ST, true>, reg_grid, st, lds);                       \
             if (e != hipSuccess) return e;                                                                \
             hipLaunchKernelGGL((k_norm_filter_reg<LL, ST, true>), reg_grid, dim3(LL / kRegPts), lds, st, in, \
-                               dmean, den, n_angles, n_rows, n, off, ft, pout);                           \
+                               dmean, den, n_angles, n_rows, n, off, run, ft, pout);                      \
         } else {                                                                                          \
             e = launch_reg<LL>(k_norm_filter_reg<LL, ST, false>, reg_grid, st, lds);                      \
             if (e != hipSuccess) return e;                                                                \
             hipLaunchKernelGGL((k_norm_filter_reg<LL, ST, false>), reg_grid, dim3(LL / kRegPts), lds, st, in, \
-                               dmean, den, n_angles, n_rows, n, off, ft, pout);                           \
+                               dmean, den, n_angles, n_rows, n, off, run, ft, pout);                      \
         }                                                                                                 \
         return hipGetLastError();
     switch (ft.L) {

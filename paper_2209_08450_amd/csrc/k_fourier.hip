@@ -521,22 +521,20 @@ k_fr_cols(const float2* __restrict__ cols, const float2* __restrict__ tw, Fourie
 // radix-16 passes exchange only their outputs through LDS; after the last
 // pass slot s holds output index t + B s in natural order.
 // ---------------------------------------------------------------------------
-// Angles per work-group of the register spectra kernel: each angle's raw
-// counts are prefetched while the previous angle is transformed.
-constexpr int kFrAnglesPerGroup = 8;
-
+// A work-group takes `run` angles (run_length): each angle's raw counts are
+// prefetched while the previous angle is transformed.
 template <int L>
 __global__ void __launch_bounds__(L / kRegPts)
 k_fr_spectra_reg(RawInput in, int rows, const float* __restrict__ dmean, const float* __restrict__ rden,
-                 const float2* __restrict__ tw, FourierTables t, uint32_t* __restrict__ spec) {
+                 const float2* __restrict__ tw, FourierTables t, int run, uint32_t* __restrict__ spec) {
     extern __shared__ float2 lds[];
     constexpr int B = L / kRegPts, h = L / 2;
     const int n = t.n, off = (L - n) / 2;
     int p, a0;
-    spectra_work((rows + 1) / 2, (t.na + kFrAnglesPerGroup - 1) / kFrAnglesPerGroup, p, a0);
+    spectra_work((rows + 1) / 2, (t.na + run - 1) / run, p, a0);
     if (2 * p >= rows) return;  // whole work-group
-    a0 *= kFrAnglesPerGroup;
-    const int a1 = min(t.na, a0 + kFrAnglesPerGroup);
+    a0 *= run;
+    const int a1 = min(t.na, a0 + run);
     const int z0 = 2 * p;
     const bool has1 = z0 + 1 < rows;
     const int64_t r0 = static_cast<int64_t>(z0) * n;
@@ -687,13 +685,14 @@ hipError_t launch_grid_nt(const FourierTables& t, const uint32_t* spec, int pair
 hipError_t launch_fourier_spectra(const RawInput& in, int rows, const float* dmean, const float* rden,
                                   const float2* tw_L, const FourierTables& t, uint32_t* spec, hipStream_t st) {
     const int pairs = (rows + 1) / 2;
+    const int run = run_length(pairs, t.na);
 #define TP_FR_REG(LL)                                                                                      \
     case LL: {                                                                                            \
-        const dim3 g(spectra_grid(pairs, (t.na + kFrAnglesPerGroup - 1) / kFrAnglesPerGroup));            \
+        const dim3 g(spectra_grid(pairs, (t.na + run - 1) / run));                                        \
         const hipError_t e = fr_lds(k_fr_spectra_reg<LL>, reg_lds(LL));                                   \
         if (e != hipSuccess) return e;                                                                    \
         hipLaunchKernelGGL((k_fr_spectra_reg<LL>), g, dim3(LL / kRegPts), reg_lds(LL), st, in, rows, dmean, rden, \
-                           tw_L, t, spec);                                                               \
+                           tw_L, t, run, spec);                                                          \
         return hipGetLastError();                                                                         \
     }
     switch (t.L) {
