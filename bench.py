@@ -37,6 +37,11 @@ UNIT = "Gvoxel-angle updates/s"
 FLOP_PER_UPDATE = 7
 # MI355X fp32 vector peak: 256 CUs x 4 SIMDs x 16 lanes x 2 (FMA) x 2 (packed) x 2.4 GHz.
 PEAK_FP32_TFLOPS = 157.3
+# MI355X dense FP16 matrix peak, and what the fused chunk's backprojection
+# issues: one 16x16x32 product (16384 flop) per 16 voxels x 4 angles x 16 slices
+# and pair of operand parts (FP16 rows 1, BF16 2, FP32 3 of them).
+PEAK_FP16_MATRIX_TFLOPS = 2500.0
+MATRIX_FLOP_PER_UPDATE = {"f16": 16, "bf16": 32, "f32": 48}
 
 
 FILTER_NAMES = {"ramp": "ramp filter", "shepp": "Shepp-Logan-windowed ramp filter",
@@ -231,27 +236,10 @@ def measure_peaks(log, copy_bytes: int = 2 << 30, fma_blocks: int = 4096, fma_it
                     f"here; best of {reps} event-timed launches"}
 
 
-def load_valu_counters(storage: str, chunk: int, n: int, angles: int):
-    """VALU wave-instructions per backprojection launch from committed
-    rocprofv3 SQ counters, if they were taken on the current kernel source and
-    this launch shape."""
-    p = os.path.join(ROOT, "profiles", "valu_backproject.json")
-    if not os.path.exists(p):
-        return None
-    try:
-        d = json.load(open(p))
-    except ValueError:
-        return None
-    e = d.get(storage)
-    if not e or d.get("kernel_sha") != kernel_source_hash():
-        return None
-    if (e.get("chunk"), e.get("n"), e.get("angles")) != (chunk, n, angles):
-        return None
-    return e
-
-
 def kernel_source_hash() -> str:
-    p = os.path.join(ROOT, "paper_2209_08450_amd", "csrc", "k_backproject.hip")
+    p = os.path.join(ROOT, "paper_2209_08450_amd", "csrc", "k_backproject_blocked.hip")
+    if not os.path.exists(p):
+        return ""
     return hashlib.sha256(open(p, "rb").read()).hexdigest()[:16]
 
 
@@ -513,25 +501,7 @@ def main():
     bp_updates = float(n) * n * na * chunk
     achieved = FLOP_PER_UPDATE * bp_updates / (r["bp_launch_ms"] * 1e-3) / 1e12
     traffic = load_traffic(head, chunk, n, na)
-    valu = load_valu_counters(head, chunk, n, na)
-    if valu is not None:
-        insts = float(valu["valu_insts_per_launch"])
-        t_launch = r["bp_launch_ms"] * 1e-3
-        # FP16 rows: one v_dot2 per slice and voxel-angle (per wave: one per 64
-        # updates), issued at the dot2 rate; every other VALU instruction at the
-        # FP32 FMA rate.  LDS: the bytes the taps read per update (an FP16 pair,
-        # or two FP32 values).
-        dot2 = bp_updates / 64.0 if head == "f16" else 0.0
-        t_valu = dot2 / peaks["dot2_wave_instructions_per_s"] + (insts - dot2) / peaks["valu_wave_instructions_per_s"]
-        lds_bytes = bp_updates * (4.0 if head == "f16" else 8.0)
-        valu = {"valu_insts_per_launch": insts, "valu_insts_per_update": round(insts * 64 / bp_updates, 3),
-                "dot2_insts_per_launch": dot2,
-                "valu_busy_frac": round(t_valu / t_launch, 4),
-                "lds_tap_bytes_per_launch": lds_bytes,
-                "lds_busy_frac": round(lds_bytes / t_launch / (peaks["lds_read_TBs"] * 1e12), 4),
-                "source": "profiles/valu_backproject.json (rocprofv3 SQ_INSTS_VALU on this kernel source); "
-                          "busy fractions: issue time at the measured dot2 and FP32 FMA rates, tap bytes at the "
-                          "measured LDS read rate, over the launch time"}
+    matrix = MATRIX_FLOP_PER_UPDATE[head] * bp_updates / (r["bp_launch_ms"] * 1e-3) / 1e12
     out = {
         "metric": METRIC,
         "value": round(r["gups"], 3),
@@ -555,17 +525,18 @@ def main():
         "precision_sampled_vs_fp64_oracle": precision,
         "stage_ms_per_step": {st: {k: round(v, 2) for k, v in results[st]["stage_ms_per_step"].items()}
                               for st in storages},
-        "roofline": {"bound": "alu", "kernel": "k_backproject", "achieved": round(achieved, 2),
-                     "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_TFLOPS, 4),
-                     "frac_of_measured_fma_rate": round(achieved / peaks["fp32_fma_nonpacked_TFLOPs"], 4),
+        "roofline": {"bound": "mfma", "kernel": "k_backproject_blocked", "achieved": round(achieved, 2),
+                     "peak": PEAK_FP16_MATRIX_TFLOPS, "unit": "TFLOP/s",
+                     "frac": round(achieved / PEAK_FP16_MATRIX_TFLOPS, 4),
                      "traffic": traffic,
                      "launch_ms": round(r["bp_launch_ms"], 3),
                      "flop_per_launch": FLOP_PER_UPDATE * bp_updates,
-                     "executed": valu,
+                     "executed": {"matrix_flop_per_update": MATRIX_FLOP_PER_UPDATE[head],
+                                  "matrix_TFLOPs": round(matrix, 2),
+                                  "matrix_frac": round(matrix / PEAK_FP16_MATRIX_TFLOPS, 4)},
                      "note": "achieved = 7 algorithmic flop per voxel-angle update / launch time; the kernel "
-                             "shares the coordinate, fraction and weights of a voxel and angle over 16 slices and "
-                             "(FP16 rows) adds both taps of a slice with one v_dot2, so it issues fewer VALU "
-                             "instructions than 7 flop per update (see executed)"},
+                             "adds 4 angles x 8 bins of 16 slices to 16 voxels with one 16x16x32 product, "
+                             "most of whose weights are zero (executed)"},
         "measured_peaks": peaks,
         # the fused normalise + filter kernel: HBM-class work (uint16 raw sample
         # in, one filtered sample out in the storage type, per sample of the
