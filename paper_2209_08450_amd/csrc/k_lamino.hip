@@ -23,19 +23,18 @@
 // LDS after the block's last read.  Slices lie at most a row apart, so G of them
 // (2, 4 or 8, by the sine of the tilt) share the rows they read: one row
 // coordinate, G + 1 window reads interpolated across the columns once, and
-// per slice two clamped fractions and two FMAs, where a slice by itself took
-// its own coordinate, address and two reads of two columns.  Bound: vector
+// per slice a selection of its two rows and one FMA, where a slice by itself
+// took its own coordinate, address and two reads of two columns.  Bound: vector
 // work (64 slices of 1024^2 from 512 FP16 projections of 1024^2, sine 0.89:
-// 13.6 ms slice by slice, 11.3 ms in groups of 8; 32 slices, 256 projections,
-// FP32: 7.2 -> 5.9 ms in groups of 2, 6.1 -> 4.6 in 4, 4.2 -> 3.1 in 8).  A
-// window with a sample that is not finite is summed slice by slice, so that it
-// reaches its own taps alone.  The column coordinate u is the
-// backprojector's split expression (the plan's tile tables, integer + FP32
-// fraction); the row coordinate v uses tables of the same split form per
-// tile edge and per slice, so both keep FP32 precision at any detector size,
-// and each slice's coordinates are the same however the volume is split into
-// calls.  Every LDS index is clamped into the staged window, which the window
-// bounds (from the tile's corners, with one sample of margin) make a no-op.
+// 13.5 ms slice by slice, 11.4 ms in groups of 8; 32 slices, 256 projections,
+// FP32: 7.2 -> 5.8 ms in groups of 2, 6.1 -> 4.6 in 4, 4.2 -> 2.9 in 8).
+// The column coordinate u is the backprojector's split expression (the plan's
+// tile tables, integer + FP32 fraction); the row coordinate v uses tables of
+// the same split form per tile edge and per slice, so both keep FP32 precision
+// at any detector size, and each slice's coordinates are the same however the
+// volume is split into calls.  Every LDS index is clamped into the staged
+// window, which the window bounds (from the tile's corners, with one sample of
+// margin) make a no-op.
 #include <type_traits>
 
 #include "tp_internal.h"
@@ -124,7 +123,6 @@ k_lamino(GeoTables g, LaminoTables t, const TI* __restrict__ filt, int z0, int n
     // the window (a sum rounded in FP32, the same for a slice in any call
     // since its block is fixed)
     __shared__ float s_cz[2][kLamA][kLamK];
-    __shared__ int s_bad[2][kLamA];  // the window holds an infinity or NaN
     const int nb = g.nb, na = g.na, N = g.N, n = g.n;
     // Work item of this work-group: the hardware hands work-group ids to the
     // XCDs round robin, and the remap gives each XCD a contiguous range of
@@ -149,15 +147,13 @@ k_lamino(GeoTables g, LaminoTables t, const TI* __restrict__ filt, int z0, int n
         iz[k] = t.vzi[z];
     }
     // slice k of a group of G from its first one's row coordinate: k - 1 whole
-    // rows (none for k = 1) and this much more, less 1 for the upper pair of taps
-    float off1[kLamK], off2[kLamK];
+    // rows (none for k = 1) and this much more, 0 to 1 but for its rounding
+    float off[kLamK];
 #pragma unroll
     for (int k = 0; k < kLamK; ++k) {
         const int b = k / G * G;
-        off1[k] = static_cast<float>(iz[k] - iz[b] - (k - b - 1)) + (fz[k] - fz[b]);
-        off2[k] = off1[k] - 1.0f;
-        asm volatile("" : "+v"(off1[k]));  // an addition with a scalar operand issues at half rate
-        if (kH) asm volatile("" : "+v"(off2[k]));
+        off[k] = fminf(fmaxf(static_cast<float>(iz[k] - iz[b] - (k - b - 1)) + (fz[k] - fz[b]), 0.0f), 1.0f);
+        asm volatile("" : "+v"(off[k]));  // an addition with a scalar operand issues at half rate
     }
     float acc[4][kLamK];
 #pragma unroll
@@ -278,7 +274,6 @@ k_lamino(GeoTables g, LaminoTables t, const TI* __restrict__ filt, int z0, int n
 #pragma unroll
             for (int m = 0; m < 3; ++m) col[m] = col_of(c0, m, &cin[m]);
             WinT* wj = reinterpret_cast<WinT*>(win_mem) + sj * wrows * kLamCols + lc;
-            float probe = 0.0f;  // NaN after any sample that is not finite
 #pragma unroll
             for (int p = 0; p < kLamPre; ++p) {
                 const int rr = lr + 4 * p, row = r0 + rr;
@@ -289,7 +284,6 @@ k_lamino(GeoTables g, LaminoTables t, const TI* __restrict__ filt, int z0, int n
                     for (int m = 0; m < 3; ++m) {
                         asm volatile("" : "+v"(X[p][m]));
                         v[m] = (rin && cin[m]) ? X[p][m] : 0u;
-                        probe = __builtin_fmaf(lam_value<__half>(v[m]), 0.0f, probe);
                     }
                     put_row_h(wj + rr * kLamCols, v, rr < nr);
                 } else {
@@ -298,7 +292,6 @@ k_lamino(GeoTables g, LaminoTables t, const TI* __restrict__ filt, int z0, int n
                     for (int m = 0; m < 3; ++m) {
                         asm volatile("" : "+v"(X[p][m]));
                         v[m] = (rin && cin[m]) ? lam_value<TI>(X[p][m]) : 0.0f;
-                        probe = __builtin_fmaf(v[m], 0.0f, probe);
                     }
                     put_row(wj + rr * kLamCols, v, rr < nr);
                 }
@@ -315,7 +308,6 @@ k_lamino(GeoTables g, LaminoTables t, const TI* __restrict__ filt, int z0, int n
                         for (int m = 0; m < 3; ++m) {
                             const uint32_t x = lam_raw(img + (base + static_cast<unsigned>(col[m])));
                             v[m] = (rin && cin[m]) ? x : 0u;
-                            probe = __builtin_fmaf(lam_value<__half>(v[m]), 0.0f, probe);
                         }
                         put_row_h(wj + rr * kLamCols, v, rr < nr);
                     } else {
@@ -324,14 +316,11 @@ k_lamino(GeoTables g, LaminoTables t, const TI* __restrict__ filt, int z0, int n
                         for (int m = 0; m < 3; ++m) {
                             const float x = load_as_float(img + (base + static_cast<unsigned>(col[m])), 0);
                             v[m] = (rin && cin[m]) ? x : 0.0f;
-                            probe = __builtin_fmaf(v[m], 0.0f, probe);
                         }
                         put_row(wj + rr * kLamCols, v, rr < nr);
                     }
                 }
             }
-            const int any = __any(probe != 0.0f);
-            if (lane == 0) s_bad[buf][sj] = any;
         }
     };
 
@@ -353,9 +342,6 @@ k_lamino(GeoTables g, LaminoTables t, const TI* __restrict__ filt, int z0, int n
         for (int j = 0; j < cnt; ++j) {
             const float cs = s_cs[cur][j], sn = s_sn[cur][j], dvx = s_dvx[cur][j], dvy = s_dvy[cur][j];
             const int ubase = s_ui[cur][j] - s_ci[cur][j];
-            // the largest row index a bilinear read may start at; the unsigned
-            // clamp also sends a negative index there (reads stay in the window)
-            const unsigned rmax = static_cast<unsigned>(s_nr[cur][j] - 2);
             const float uf = s_uf[cur][j];
             // bilinear samples of a window column, by the fraction between its two columns
             auto across = [&](const WinT& e, float wu) {
@@ -368,52 +354,17 @@ k_lamino(GeoTables g, LaminoTables t, const TI* __restrict__ filt, int z0, int n
                     return __builtin_fmaf(wu, e.y, e.x);
                 }
             };
-            if (!__builtin_amdgcn_readfirstlane(s_bad[cur][j])) {
-                // G slices at a time: sin(tilt) <= 1 row apart, so slice k lies 0 to 2
-                // rows past row k - 1 of its group, and is the sum
-                //   h[k - 1] + clamp(t) (h[k] - h[k - 1]) + clamp(t - 1) (h[k + 1] - h[k])
-                // of rows that the group reads and interpolates across once
-                const unsigned rlast = static_cast<unsigned>(s_nr[cur][j] - 1 - G);
-                float base[kLamK / G];
+            // G slices at a time: sin(tilt) <= 1 row apart, so slice k lies 0 to 2 rows
+            // past row k - 1 of its group and takes rows k - 1 and k, or k and k + 1,
+            // of the rows that the group reads and interpolates across once.  The two
+            // are selected, not weighted: a row that a slice does not read, however
+            // large, infinite or not a number, leaves its sum alone.
+            // The unsigned clamp to the last row a group may start at also sends a
+            // negative index there (reads stay in the window).
+            const unsigned rlast = static_cast<unsigned>(s_nr[cur][j] - 1 - G);
+            float base[kLamK / G];
 #pragma unroll
-                for (int b = 0; b < kLamK / G; ++b) base[b] = s_cz[cur][j][b * G];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float dy = static_cast<float>(ty + 8 * i);
-                    const float u = tile_offset(dx, dy, cs, sn, uf);
-                    const int c = min(max(coord_floor(u) + ubase, 0), kLamCols - 2);
-                    const float wu = coord_frac(u);
-                    const float va = __builtin_fmaf(dx, dvx, dy * dvy);
-                    const unsigned cb = static_cast<unsigned>((j * wrows * kLamCols + c) * sizeof(WinT));
-#pragma unroll
-                    for (int b = 0; b < kLamK / G; ++b) {
-                        const float v = va + base[b];
-                        const unsigned r = min(static_cast<unsigned>(coord_floor(v)), rlast);
-                        const float w = coord_frac(v);
-                        const WinT* p = reinterpret_cast<const WinT*>(
-                            reinterpret_cast<const char*>(win_mem) + (__umul24(r, kLamCols * sizeof(WinT)) + cb));
-                        WinT e[G + 1];
-#pragma unroll
-                        for (int q = 0; q <= G; ++q) e[q] = p[q * kLamCols];
-                        float h = across(e[0], wu), h1 = across(e[1], wu), d = h1 - h;
-                        acc[i][b * G] = __builtin_fmaf(w, d, acc[i][b * G] + h);
-#pragma unroll
-                        for (int q = 1; q < G; ++q) {
-                            const int k = b * G + q;
-                            const float h2 = across(e[q + 1], wu), d1 = h2 - h1;
-                            const float c1 = __builtin_amdgcn_fmed3f(w + off1[k], 0.0f, 1.0f);
-                            // (FP32 pairs leave no registers for the second set)
-                            const float c2 = __builtin_amdgcn_fmed3f(kH ? w + off2[k] : (w + off1[k]) - 1.0f, 0.0f, 1.0f);
-                            acc[i][k] = __builtin_fmaf(c2, d1, __builtin_fmaf(c1, d, acc[i][k] + h));
-                            h = h1;
-                            h1 = h2;
-                            d = d1;
-                        }
-                    }
-                }
-                continue;
-            }
-            // an infinity or NaN in the window: each slice from its own two rows alone
+            for (int b = 0; b < kLamK / G; ++b) base[b] = s_cz[cur][j][b * G];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float dy = static_cast<float>(ty + 8 * i);
@@ -423,14 +374,28 @@ k_lamino(GeoTables g, LaminoTables t, const TI* __restrict__ filt, int z0, int n
                 const float va = __builtin_fmaf(dx, dvx, dy * dvy);
                 const unsigned cb = static_cast<unsigned>((j * wrows * kLamCols + c) * sizeof(WinT));
 #pragma unroll
-                for (int k = 0; k < kLamK; ++k) {
-                    const float v = va + s_cz[cur][j][k];  // row in the window
-                    const unsigned r = min(static_cast<unsigned>(coord_floor(v)), rmax);
+                for (int b = 0; b < kLamK / G; ++b) {
+                    const float v = va + base[b];
+                    const unsigned r = min(static_cast<unsigned>(coord_floor(v)), rlast);
+                    const float w = fminf(coord_frac(v), 0x1.fffffcp-1f);  // plus 1 still rounds below 2
                     const WinT* p = reinterpret_cast<const WinT*>(
                         reinterpret_cast<const char*>(win_mem) + (__umul24(r, kLamCols * sizeof(WinT)) + cb));
-                    const float top = across(p[0], wu), bot = across(p[kLamCols], wu);
-                    acc[i][k] += __builtin_fmaf(coord_frac(v), bot - top, top);
-                    __builtin_amdgcn_sched_barrier(0);
+                    WinT e[G + 1];
+#pragma unroll
+                    for (int q = 0; q <= G; ++q) e[q] = p[q * kLamCols];
+                    float h = across(e[0], wu), h1 = across(e[1], wu), d = h1 - h;
+                    acc[i][b * G] += __builtin_fmaf(w, d, h);
+#pragma unroll
+                    for (int q = 1; q < G; ++q) {
+                        const int k = b * G + q;
+                        const float h2 = across(e[q + 1], wu), d1 = h2 - h1;
+                        const float past = w + off[k];
+                        const bool up = past >= 1.0f;
+                        acc[i][k] += __builtin_fmaf(coord_frac(past), up ? d1 : d, up ? h1 : h);
+                        h = h1;
+                        h1 = h2;
+                        d = d1;
+                    }
                 }
             }
         }
