@@ -81,7 +81,7 @@ __device__ __forceinline__ uint32_t* spectra_row(uint32_t* spec, int p, int slot
 }
 __device__ __forceinline__ void spectra_store(uint32_t* row, int k, int SL, float2 v) {
     uint32_t hi, lo;
-    split_pair(v.x, v.y, hi, lo);
+    split_data(v.x, v.y, hi, lo);
     row[static_cast<int64_t>(k) * kFrPairGroup] = hi;
     row[(static_cast<int64_t>(SL) + k) * kFrPairGroup] = lo;
 }
@@ -159,8 +159,13 @@ k_fr_spectra(RawInput in, int rows, const float* __restrict__ dmean, const float
 // sample): three such groups of 8 per angle.
 //
 // Precision: weights and samples are two FP16 values each (the rounded value
-// and what it misses) and three products are summed, the dropped one below
-// 2^-22 of the whole; 4 angles at a time are summed from zero and added once, and
+// and what it misses, the samples' kept 2^11 times as large: see split_data) and
+// three products are summed, the dropped one below 2^-22 of the whole.  The
+// samples' scale is set by the largest row there can be, a line integral of
+// 13.8, so those of a faint object lie far down FP16's range; with the second
+// value unscaled, and so subnormal, the error was 1.7e-5 at a largest line
+// integral of 0.001, now 4.6e-7 as at 1 (100 angles, 160 columns).
+// 4 angles at a time are summed from zero and added once, and
 // where more than 128 angles meet (tiles around the origin) FP64 totals take
 // up the FP32 sums every 64 angles.  The weights are not cut off at the
 // truncation radius: every sample that a window holds counts.
@@ -357,12 +362,16 @@ __device__ __forceinline__ void gather_tile(const FourierTables& t, const u4_t* 
                 }
 #pragma unroll
                 for (int n = 0; n < NT; ++n) {
-                    const u4_t x = read_slots(src + n * kTile), y = read_slots(src + n * kTile + kPlane);
+                    const u4_t x = read_slots(src + n * kTile);
                     if constexpr (first.value) sum[n] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
-                    sum[n] = mfma16(lo, x, sum[n]);  // smallest products first
-                    sum[n] = mfma16(hi, y, sum[n]);
+                    sum[n] = mfma16(lo, x, sum[n]);  // the smaller product first
                     sum[n] = mfma16(hi, x, sum[n]);
                 }
+                // (after the others: the weights take the place of the first ones)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) hi[j] = low_weights(hi[j]);
+#pragma unroll
+                for (int n = 0; n < NT; ++n) sum[n] = mfma16(hi, read_slots(src + n * kTile + kPlane), sum[n]);
             };
             unit(std::true_type{}, q0, rowp);
             float q = q0;

@@ -82,5 +82,22 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t& hi, uint3
     lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, half2_t));
 }
 
+// Data in two FP16 values: the second, what the first misses, is kept 2^11 times
+// as large, of the first one's magnitude, so that it is normal wherever the
+// first is: the pair keeps its 22 bits (and a sign) 11 binades further down.
+// Its products take weights 2^-11 times as large.
+constexpr float kLowScale = 2048.0f;
+__device__ __forceinline__ void split_data(float x, float y, uint32_t& hi, uint32_t& lo) {
+    const half2_t h = __builtin_convertvector((f2_t{x, y}), half2_t);
+    const f2_t r{(x - static_cast<float>(h.x)) * kLowScale, (y - static_cast<float>(h.y)) * kLowScale};
+    hi = __builtin_bit_cast(uint32_t, h);
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, half2_t));
+}
+// Weights in [0, 1] for the second values (below 2^-3 they round at 2^-25).
+__device__ __forceinline__ uint32_t low_weights(uint32_t hi) {
+    constexpr _Float16 s = static_cast<_Float16>(1.0f / kLowScale);
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, hi) * half2_t{s, s});
+}
+
 }  // namespace
 }  // namespace tp

@@ -59,7 +59,7 @@ struct RawInput {
 // pairs of slices and per angle in the order of the angles reduced modulo pi
 // (sorted), each row holding the L + 1 samples of signed frequency k = -L/2 ..
 // L/2 at index k + L/2 (reversed for angles whose reduction flipped the ray
-// direction), as two FP16 planes (the rounded sample and what it misses):
+// direction), as two FP16 planes (the rounded sample and 2^11 times what it misses):
 //   spec[group][angle][plane][sample][pair of the group][re, im].
 // 2^(2 e) scales the samples into FP16's range: with counts clamped before the
 // logarithm none exceeds 2^15.
