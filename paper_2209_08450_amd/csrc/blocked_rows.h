@@ -3,7 +3,7 @@
 //   rows[z / 8][angle][plane][bin][z % 8],
 // so that a window of bins is one contiguous piece for 8 slices, read 16 bytes
 // per lane straight into LDS.  FP32 rows take two FP16 planes (the rounded
-// sample and what it misses), the same 4 bytes.  In sinogram order the 64 rows
+// sample and 2^11 times what it misses), the same 4 bytes.  In sinogram order the 64 rows
 // of a window lie a power of two apart: the loads then queue on few sets of the
 // first-level cache (they cost 12 to 30 ms of 128 rows of the 2048-cubed scan).
 #pragma once
@@ -19,11 +19,11 @@ enum { kStF16 = 0, kStBF16 = 1, kStF32 = 2 };
 template <int ST> struct Blocked;
 template <> struct Blocked<kStF16> { static constexpr int PB = 1, PA = 1, A = 8; };
 template <> struct Blocked<kStBF16> { static constexpr int PB = 1, PA = 2, A = 8; };
-template <> struct Blocked<kStF32> { static constexpr int PB = 2, PA = 2, A = 4; };
+template <> struct Blocked<kStF32> { static constexpr int PB = 2, PA = 2, A = 8; };
 
-// A power of two that keeps both halves of a split row normal: rows stay below
-// 7 (13.82 = -ln 1e-6 times the filters' absolute sum of at most 1/2), 2^12
-// times them below 65504.
+// A power of two that puts the rows high in FP16's range: they stay below 7
+// (13.82 = -ln 1e-6 times the filters' absolute sum of at most 1/2), 2^12 times
+// them below 65504.
 constexpr float kRowScale = 4096.0f;
 
 // Sample v of bin j: `row` points at (z / 8, angle, plane 0, bin 0, z % 8).
@@ -37,7 +37,7 @@ template <int ST> __device__ __forceinline__ void store_blocked(uint16_t* row, i
         const float s = v * kRowScale;
         const __half hi = __float2half_rn(s);
         row[8 * static_cast<int64_t>(j)] = __half_as_ushort(hi);
-        row[8 * (static_cast<int64_t>(n) + j)] = __half_as_ushort(__float2half_rn(s - __half2float(hi)));
+        row[8 * (static_cast<int64_t>(n) + j)] = __half_as_ushort(__float2half_rn((s - __half2float(hi)) * kLowScale));
     }
 }
 

@@ -82,11 +82,8 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t& hi, uint3
     lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, half2_t));
 }
 
-// Data in two FP16 values: the second, what the first misses, is kept 2^11 times
-// as large, of the first one's magnitude, so that it is normal wherever the
-// first is: the pair keeps its 22 bits (and a sign) 11 binades further down.
-// Its products take weights 2^-11 times as large.
-constexpr float kLowScale = 2048.0f;
+// Data as two FP16 values (kLowScale).  Products of the second take weights
+// 2^-11 times as large.
 __device__ __forceinline__ void split_data(float x, float y, uint32_t& hi, uint32_t& lo) {
     const half2_t h = __builtin_convertvector((f2_t{x, y}), half2_t);
     const f2_t r{(x - static_cast<float>(h.x)) * kLowScale, (y - static_cast<float>(h.y)) * kLowScale};

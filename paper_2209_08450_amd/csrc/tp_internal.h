@@ -229,6 +229,11 @@ __device__ __forceinline__ int coord_floor(float s) {
 // the hardware instruction (only differs for |s| < 2^-24 below an integer).
 __device__ __forceinline__ float coord_frac(float s) { return __builtin_amdgcn_fractf(s); }
 
+// Data in two FP16 values: the second, what the first misses, is kept this much
+// larger, of the first one's magnitude, so that it is normal wherever the first
+// is: the pair keeps its 22 bits (and a sign) 11 binades further down.
+constexpr float kLowScale = 2048.0f;
+
 // ---- storage conversions (round to nearest even) ----
 // Negative log of the flat/dark-corrected transmission (paper, Section 2.2):
 // -ln(max((P - D) * rden, 1e-6)) with rden = 1 / max(F - D, 1) stored per

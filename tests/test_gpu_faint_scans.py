@@ -53,7 +53,7 @@ def _error(tp, path, contrast):
 # A relative error is the same at every contrast; a factor 2 for what the
 # coarser steps of the counts make of the image.
 @pytest.mark.parametrize("contrast", [1e-2, 1e-3, 1e-4])
-@pytest.mark.parametrize("path", ["fourier"])
+@pytest.mark.parametrize("path", ["fourier", "f32"])
 def test_error_does_not_grow_as_absorption_falls(tp, path, contrast):
     note(f"faint scan {path} {contrast:g}")
     full, faint = _error(tp, path, 1.0), _error(tp, path, contrast)
