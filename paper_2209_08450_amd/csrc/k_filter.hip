@@ -81,10 +81,6 @@ __device__ __forceinline__ void blocked_work(int n_rows, int pieces, int& r, int
     piece = item % pieces;
     r = item / pieces * 8 + s % high;
 }
-unsigned blocked_grid(int n_rows, int pieces) {
-    const int64_t items = static_cast<int64_t>((n_rows + 7) / 8) * pieces;
-    return static_cast<unsigned>((items + 7) / 8 * 8 * (n_rows < 8 ? n_rows : 8));
-}
 
 // Rows (r, a) and (r, a + 1) of the chunk, a even; raw counts normalised in registers.
 template <int ST>
@@ -347,9 +343,9 @@ hipError_t launch_norm_filter_t(const RawInput& in, const float* dmean, const fl
                                 int n_rows, int n, const FilterTables& ft, void* out, hipStream_t st) {
     const int off = (ft.L - n) / 2;
     const int pairs = (n_angles + 1) / 2;
-    const dim3 grid(blocked_grid(n_rows, pairs));
+    const dim3 grid(static_cast<unsigned>(blocked_groups(n_rows, pairs)));  // < 2^31 (checked by the host)
     const int run = run_length(n_rows, pairs);
-    const dim3 reg_grid(blocked_grid(n_rows, (pairs + run - 1) / run));
+    const dim3 reg_grid(static_cast<unsigned>(blocked_groups(n_rows, (pairs + run - 1) / run)));
     uint16_t* pout = static_cast<uint16_t*>(out);
     size_t lds = 0;
     hipError_t e = hipSuccess;

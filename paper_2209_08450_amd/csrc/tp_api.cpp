@@ -1339,7 +1339,7 @@ tp_status tp_fbp_chunk_out(const tp_plan* plan, const uint16_t* proj, int64_t pr
     if (reinterpret_cast<uintptr_t>(workspace) & 255) return fail(TP_EINVAL, "workspace not 256-byte aligned");
     const size_t need = tp_fbp_workspace_bytes(plan, n_rows, storage);
     if (workspace_bytes < need) return fail(TP_EINVAL, "workspace %zu < %zu bytes", workspace_bytes, need);
-    if (static_cast<int64_t>(n_rows) * ((plan->na + 1) / 2) > 0x7fffffffLL)
+    if (tp::blocked_groups(n_rows, (plan->na + 1) / 2) > 0x7fffffffLL)
         return fail(TP_EINVAL, "n_rows=%d x n_angles=%d too large for one call", n_rows, plan->na);
     auto st = static_cast<hipStream_t>(stream);
     tp::FilterTables ft = plan->filt;
@@ -1465,7 +1465,8 @@ tp_status tp_fourier_fbp_chunk_out(const tp_plan* plan, const uint16_t* proj, in
     P = std::min<int64_t>(std::max<int64_t>(P, 1), pairs);
     // work-groups of the gather per pass: at most one per 16x16 tile of half a grid and pair
     const int64_t tiles = static_cast<int64_t>(d.M / 16) * (d.M / 32 + 2);
-    P = std::min<int64_t>(P, 0x7fffffffLL / std::max<int64_t>({tiles, plan->na + 8, d.M}));
+    // (spectra: whole groups of four pairs, dealt to the 8 XCDs in turn)
+    P = std::min<int64_t>(P, 0x7fffffffLL / std::max<int64_t>({tiles, plan->na + 8, d.M}) - 3);
     while (P > 1 && fr_workspace(plan, n_rows, P) > workspace_bytes) --P;
     if (P > tp::kFrPairGroup && P < pairs) P -= P % tp::kFrPairGroup;  // whole groups of pairs in every pass
     if (P < 1) return fail(TP_EINVAL, "grid too large for one launch");

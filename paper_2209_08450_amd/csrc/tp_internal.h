@@ -153,6 +153,12 @@ hipError_t launch_filter(const void* in, tp_dtype in_dt, void* out, tp_dtype out
 hipError_t launch_norm_filter(const RawInput& in, const float* dmean, const float* den, int n_angles,
                               int n_rows, int n_det, const FilterTables& ft, tp_dtype out_dt, void* out,
                               hipStream_t st);
+// Work-groups of launch_norm_filter for `pieces` pieces of a slice's angles:
+// whole blocks of 8 slices, dealt to the 8 XCDs in turn.
+inline int64_t blocked_groups(int n_rows, int pieces) {
+    const int64_t items = static_cast<int64_t>((n_rows + 7) / 8) * pieces;
+    return (items + 7) / 8 * 8 * (n_rows < 8 ? n_rows : 8);
+}
 // Blocked filtered rows (blocked_rows.h): their bytes, and their backprojection.
 size_t blocked_rows_bytes(int n_rows, int na, int n, tp_dtype dt);
 hipError_t launch_backproject_blocked(const GeoTables& g, const void* rows, tp_dtype dt, int n_rows, float scale,
