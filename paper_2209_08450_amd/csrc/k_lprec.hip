@@ -390,7 +390,8 @@ k_lp_conv_residue(const float2* __restrict__ ghat, LprecTables t, int pairs, flo
     __syncthreads();
     reg_fft<NAc>(X, mine, t.twNAc, tid);
     const float2* kcol = t.kt + static_cast<int64_t>(eta) * t.NA;
-    float2* dst = fhat + (static_cast<int64_t>(p) * t.spans + span) * t.residues * t.nqb * NS * kLpRows + eta * kLpRows;
+    float2* dst = fhat + ((static_cast<int64_t>(p) * t.spans + span) * t.nqb * NS + eta) * kLpRows;
+    const int rows0 = t.rows / t.residues, rest = t.rows - rows0 * t.residues;
 #pragma unroll 1
     for (int r = 0; r < t.residues; ++r) {
         // an opaque thread index per residue keeps twiddles and offsets from
@@ -402,12 +403,12 @@ k_lp_conv_residue(const float2* __restrict__ ghat, LprecTables t, int pairs, flo
         for (int s = 0; s < kRegPts; ++s) x[s] = cconj(cmul(X[s], kcol[ti + B * s]));
         kcol += NAc;
         reg_fft<NAc>(x, mine, t.twNAc, ti);
+        const int place = ti + r * rows0 + min(r, rest);  // this residue's rows lie behind those of the ones before
+        float2* d = dst + static_cast<int64_t>(place / kLpRows) * NS * kLpRows + place % kLpRows;
 #pragma unroll
         for (int s = 0; s < kRegPts; ++s) {
-            const int q = ti + B * s;
-            if (q * t.residues + r < t.rows) dst[static_cast<int64_t>(q / kLpRows) * NS * kLpRows + q % kLpRows] = cconj(x[s]);
+            if ((ti + B * s) * t.residues + r < t.rows) d[static_cast<int64_t>(B / kLpRows * s) * NS * kLpRows] = cconj(x[s]);
         }
-        dst += static_cast<int64_t>(t.nqb) * NS * kLpRows;
     }
 }
 
@@ -469,13 +470,15 @@ k_lp_sigma(const float2* __restrict__ fhat, LprecTables t, int pairs, float2* __
     const int xcd = id & 7, r = id >> 3;
     const int r2 = r % kLpRows;
     const int64_t gidx = static_cast<int64_t>(r / kLpRows) * 8 + xcd;
-    const int64_t G = static_cast<int64_t>(pairs) * t.spans * t.residues * t.nqb;
+    const int64_t G = static_cast<int64_t>(pairs) * t.spans * t.nqb;
     if (gidx >= G) return;  // whole work-group
-    const int64_t psr = gidx / t.nqb;  // (pair * spans + span) * residues + residue
-    const int64_t ps = psr / t.residues;
-    const int q = static_cast<int>(gidx - psr * t.nqb) * kLpRows + r2;
-    const int m = q * t.residues + static_cast<int>(psr - ps * t.residues);
-    if (m >= t.rows) return;
+    const int64_t ps = gidx / t.nqb;  // pair * spans + span
+    const int place = static_cast<int>(gidx - ps * t.nqb) * kLpRows + r2;
+    if (place >= t.rows) return;
+    // the first `rest` residues have one row more than the others
+    const int rows0 = t.rows / t.residues, rest = t.rows - rows0 * t.residues, more = rest * (rows0 + 1);
+    const int res = place < more ? place / (rows0 + 1) : rest + (place - more) / rows0;
+    const int m = (place - res * rows0 - min(res, rest)) * t.residues + res;
     const float2* src = fhat + gidx * NS * kLpRows + r2;
     float2 x[kRegPts];
 #pragma unroll
@@ -598,7 +601,7 @@ hipError_t launch_residue_t(const LprecTables& t, const float2* ghat, int pairs,
 
 template <int NS>
 hipError_t launch_sigma_t(const LprecTables& t, const float2* fhat, int pairs, float2* F, hipStream_t st) {
-    const int64_t G = static_cast<int64_t>(pairs) * t.spans * t.residues * t.nqb;
+    const int64_t G = static_cast<int64_t>(pairs) * t.spans * t.nqb;
     const int64_t blocks = (G + 7) / 8 * 8 * kLpRows;
     hipLaunchKernelGGL(k_lp_sigma<NS>, dim3(static_cast<unsigned>(blocks)), dim3(NS / kRegPts), reg_lds_bytes(NS),
                        st, fhat, t, pairs, F);

@@ -730,8 +730,7 @@ struct LpSizes {
 
 LpSizes lp_sizes(const tp_plan* plan, const tp_lprec_grid& g) {
     const int L = plan->filt.L;
-    const int residues = tp::lprec_by_residue(g.NA / g.M) ? g.M : 1;
-    const size_t groups = static_cast<size_t>(residues) * (((g.rows + residues - 1) / residues + tp::kLpRows - 1) / tp::kLpRows);
+    const size_t groups = static_cast<size_t>((g.rows + tp::kLpRows - 1) / tp::kLpRows);
     LpSizes z;
     z.rows = sizeof(float2) * static_cast<size_t>(plan->na) * 2 * L;
     z.ghat = sizeof(float2) * static_cast<size_t>(g.spans) * g.Ns * g.n_span;
@@ -853,7 +852,7 @@ tp_status lprec_tables(const tp_plan* plan, tp_filter_kind kind, const tp_lprec_
     t.D = g.D;
     t.rows = g.rows;
     t.residues = tp::lprec_by_residue(NAc) ? g.M : 1;
-    t.nqb = ((g.rows + t.residues - 1) / t.residues + tp::kLpRows - 1) / tp::kLpRows;
+    t.nqb = (g.rows + tp::kLpRows - 1) / tp::kLpRows;
     t.m_lo = g.m_lo;
     t.j_lo = g.j_lo;
     t.nj = g.nj;

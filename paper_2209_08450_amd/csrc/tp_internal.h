@@ -129,8 +129,8 @@ struct LprecTables {
     const float2* twNAc;    // [2 NAc]
     const float2* kt;       // [Ns][NA] transformed kernel columns, prefilter and scale folded in: by residue (by_residue) or whole
     int na, n, N, L, log2L, spans, n_span, Ns, NA, M, NAc, log2NAc, D, rows, m_lo, j_lo, nj;
-    int residues;           // fhat holds row m as row m / residues of residue m % residues
-    int nqb;                // groups of kLpRows such rows
+    int residues;           // fhat holds row m as row m / residues of residue m % residues, residue after residue
+    int nqb;                // groups of kLpRows rows
     double a0, sigma0, delta, phi0, dpsi;
 };
 
