@@ -278,7 +278,10 @@ tp_status tp_radon(const tp_plan* plan, const float* vol, int32_t n_rows, float*
  * kind: filter window at the plan's pad length 2^ceil(log2(2 n_det)); windows
  * other than TP_RAMP build their tables on first use (tp_filter_prepare first
  * when the call will be graph-captured; else TP_EUNSUPPORTED during capture).
- * workspace: dev, 256-byte aligned, >= tp_fbp_workspace_bytes(plan, n_rows, storage).
+ * workspace: dev, 256-byte aligned, tp_fbp_workspace_bytes(plan, n_rows, storage)
+ * bytes, which hold whole blocks.  At least tp_normalize_workspace_bytes(n_rows,
+ * n_det) plus n_rows * n_angles * n_det samples of `storage` rounded up to 256
+ * bytes: the same slices, in passes (in a narrower block below 8), slower.
  * ------------------------------------------------------------------------ */
 size_t tp_fbp_workspace_bytes(const tp_plan* plan, int32_t n_rows, tp_dtype storage);
 tp_status tp_fbp_chunk(const tp_plan* plan,
@@ -292,8 +295,8 @@ tp_status tp_fbp_chunk(const tp_plan* plan,
 /* As tp_fbp_chunk, and additionally records caller-created hipEvent_t handles
  * (passed as void*) on `stream`: events[0] before the dark/flat means,
  * events[1] before the fused normalise+filter, events[2] before the
- * backprojection, events[3] after it.  Any entry may be NULL; events may be
- * NULL.  For per-stage timing (the paper's timeline breakdown, Section 2.3). */
+ * backprojection (of the first pass), events[3] after it (the last).  Any entry
+ * may be NULL; events may be NULL.  For per-stage timing (the paper's timeline breakdown, Section 2.3). */
 tp_status tp_fbp_chunk_events(const tp_plan* plan,
                               const uint16_t* proj, int64_t proj_stride,
                               const uint16_t* dark, int32_t n_dark,

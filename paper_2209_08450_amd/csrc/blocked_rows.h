@@ -6,6 +6,8 @@
 // sample and 2^11 times what it misses), the same 4 bytes.  In sinogram order the 64 rows
 // of a window lie a power of two apart: the loads then queue on few sets of the
 // first-level cache (they cost 12 to 30 ms of 128 rows of the 2048-cubed scan).
+// Without room for whole blocks, fewer than 8 slices lie in one block as wide as
+// there are.
 #pragma once
 
 #include "tp_internal.h"
@@ -26,18 +28,20 @@ template <> struct Blocked<kStF32> { static constexpr int PB = 2, PA = 2, A = 8;
 // them below 65504.
 constexpr float kRowScale = 4096.0f;
 
-// Sample v of bin j: `row` points at (z / 8, angle, plane 0, bin 0, z % 8).
-template <int ST> __device__ __forceinline__ void store_blocked(uint16_t* row, int n, int j, float v) {
+// Sample v of bin j: `row` points at (z / 8, angle, plane 0, bin 0, z % 8) of
+// blocks `wide` slices wide.
+template <int ST> __device__ __forceinline__ void store_blocked(uint16_t* row, int n, int wide, int j, float v) {
+    const int at = __mul24(j, wide);
     if constexpr (ST == kStF16) {
-        row[8 * static_cast<int64_t>(j)] = __half_as_ushort(__float2half_rn(v));
+        row[at] = __half_as_ushort(__float2half_rn(v));
     } else if constexpr (ST == kStBF16) {
         const float b = __uint_as_float(static_cast<uint32_t>(f32_to_bf16_rne(v)) << 16);
-        row[8 * static_cast<int64_t>(j)] = __half_as_ushort(__float2half_rn(b * kRowScale));
+        row[at] = __half_as_ushort(__float2half_rn(b * kRowScale));
     } else {
         const float s = v * kRowScale;
         const __half hi = __float2half_rn(s);
-        row[8 * static_cast<int64_t>(j)] = __half_as_ushort(hi);
-        row[8 * (static_cast<int64_t>(n) + j)] = __half_as_ushort(__float2half_rn((s - __half2float(hi)) * kLowScale));
+        row[at] = __half_as_ushort(hi);
+        row[n * wide + at] = __half_as_ushort(__float2half_rn((s - __half2float(hi)) * kLowScale));
     }
 }
 

@@ -67,9 +67,9 @@ k_filter(const TI* in, TO* out, int64_t n_lines, int n, int off, FilterTables ft
     }
 }
 
-// Where slice r's rows of angle a start in the blocked layout.
-template <int ST> __device__ __forceinline__ uint16_t* blocked_row(uint16_t* out, int r, int a, int na, int n) {
-    return out + 8 * ((static_cast<int64_t>(r >> 3) * na + a) * (Blocked<ST>::PB * static_cast<int64_t>(n))) + (r & 7);
+// Where slice r's rows of angle a start in the blocked layout, `wide` slices to a block.
+template <int ST> __device__ __forceinline__ uint16_t* blocked_row(uint16_t* out, int r, int a, int na, int n, int wide) {
+    return out + wide * ((static_cast<int64_t>(r >> 3) * na + a) * (Blocked<ST>::PB * static_cast<int64_t>(n))) + (r & 7);
 }
 
 // Work-group -> (slice r, piece of its angles): work-groups go to the 8 XCDs in
@@ -86,7 +86,7 @@ __device__ __forceinline__ void blocked_work(int n_rows, int pieces, int& r, int
 template <int ST>
 __global__ void __launch_bounds__(1024)
 k_norm_filter(RawInput in, const float* __restrict__ dmean, const float* __restrict__ den, int n_angles,
-              int n_rows, int n, int off, FilterTables ft, uint16_t* out) {
+              int n_rows, int n, int off, int wide, FilterTables ft, uint16_t* out) {
     extern __shared__ float2 buf[];
     const int tid = threadIdx.x, B = blockDim.x;
     const int pairs = (n_angles + 1) >> 1;
@@ -107,12 +107,12 @@ k_norm_filter(RawInput in, const float* __restrict__ dmean, const float* __restr
     }
     __syncthreads();
     filter_in_lds(buf, n, off, ft);
-    uint16_t* o0 = blocked_row<ST>(out, r, a0, n_angles, n);
-    uint16_t* o1 = o0 + 8 * Blocked<ST>::PB * static_cast<int64_t>(n);
+    uint16_t* o0 = blocked_row<ST>(out, r, a0, n_angles, n, wide);
+    uint16_t* o1 = o0 + wide * Blocked<ST>::PB * static_cast<int64_t>(n);
     for (int j = tid; j < n; j += B) {
         const float2 y = buf[off + j];
-        store_blocked<ST>(o0, n, j, y.x);
-        if (has1) store_blocked<ST>(o1, n, j, 0.0f - y.y);
+        store_blocked<ST>(o0, n, wide, j, y.x);
+        if (has1) store_blocked<ST>(o1, n, wide, j, 0.0f - y.y);
     }
 }
 
@@ -180,7 +180,7 @@ k_filter_reg(const TI* in, TO* out, int64_t n_lines, int n, int off, FilterTable
 template <int L, int ST, bool HALF>
 __global__ void __launch_bounds__(L / kRegPts, L == 4096 ? 3 : 1)
 k_norm_filter_reg(RawInput in, const float* __restrict__ dmean, const float* __restrict__ rden, int n_angles, int n_rows,
-                  int n, int off, int run, FilterTables ft, uint16_t* out) {
+                  int n, int off, int wide, int run, FilterTables ft, uint16_t* out) {
     extern __shared__ float2 lds[];
     constexpr int B = L / kRegPts;
     const int pairs = (n_angles + 1) >> 1;
@@ -257,15 +257,15 @@ k_norm_filter_reg(RawInput in, const float* __restrict__ dmean, const float* __r
             x[s] = make_float2(x[s].x * h, 0.0f - x[s].y * h);
         }
         reg_fft_w<L>(x, lds, w, t);
-        uint16_t* o0 = blocked_row<ST>(out, r, a0, n_angles, n);
-        uint16_t* o1 = o0 + 8 * Blocked<ST>::PB * static_cast<int64_t>(n);
+        uint16_t* o0 = blocked_row<ST>(out, r, a0, n_angles, n, wide);
+        uint16_t* o1 = o0 + wide * Blocked<ST>::PB * static_cast<int64_t>(n);
 #pragma unroll
         for (int s = 0; s < kRegPts; ++s) {
             if (HALF && (s < 4 || s >= 12)) continue;
             const int j = t + B * s - off;
             if (HALF || (j >= 0 && j < n)) {
-                store_blocked<ST>(o0, n, j, x[s].x);
-                if (has1) store_blocked<ST>(o1, n, j, 0.0f - x[s].y);
+                store_blocked<ST>(o0, n, wide, j, x[s].x);
+                if (has1) store_blocked<ST>(o1, n, wide, j, 0.0f - x[s].y);
             }
         }
 #pragma unroll
@@ -340,7 +340,7 @@ hipError_t launch_filter_in(const void* in, tp_dtype out_dt, void* out, int64_t 
 
 template <int ST>
 hipError_t launch_norm_filter_t(const RawInput& in, const float* dmean, const float* den, int n_angles,
-                                int n_rows, int n, const FilterTables& ft, void* out, hipStream_t st) {
+                                int n_rows, int n, const FilterTables& ft, int wide, void* out, hipStream_t st) {
     const int off = (ft.L - n) / 2;
     const int pairs = (n_angles + 1) / 2;
     const dim3 grid(static_cast<unsigned>(blocked_groups(n_rows, pairs)));  // < 2^31 (checked by the host)
@@ -355,12 +355,12 @@ hipError_t launch_norm_filter_t(const RawInput& in, const float* dmean, const fl
             e = launch_reg<LL>(k_norm_filter_reg<LL, ST, true>, reg_grid, st, lds);                       \
             if (e != hipSuccess) return e;                                                                \
             hipLaunchKernelGGL((k_norm_filter_reg<LL, ST, true>), reg_grid, dim3(LL / kRegPts), lds, st, in, \
-                               dmean, den, n_angles, n_rows, n, off, run, ft, pout);                      \
+                               dmean, den, n_angles, n_rows, n, off, wide, run, ft, pout);                \
         } else {                                                                                          \
             e = launch_reg<LL>(k_norm_filter_reg<LL, ST, false>, reg_grid, st, lds);                      \
             if (e != hipSuccess) return e;                                                                \
             hipLaunchKernelGGL((k_norm_filter_reg<LL, ST, false>), reg_grid, dim3(LL / kRegPts), lds, st, in, \
-                               dmean, den, n_angles, n_rows, n, off, run, ft, pout);                      \
+                               dmean, den, n_angles, n_rows, n, off, wide, run, ft, pout);                \
         }                                                                                                 \
         return hipGetLastError();
     switch (ft.L) {
@@ -375,7 +375,7 @@ hipError_t launch_norm_filter_t(const RawInput& in, const float* dmean, const fl
     e = ensure_lds(k_norm_filter<ST>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_norm_filter<ST>), grid, dim3(filter_block(ft.L)), lds, st, in, dmean, den, n_angles,
-                       n_rows, n, off, ft, pout);
+                       n_rows, n, off, wide, ft, pout);
     return hipGetLastError();
 }
 
@@ -392,13 +392,13 @@ hipError_t launch_filter(const void* in, tp_dtype in_dt, void* out, tp_dtype out
 }
 
 hipError_t launch_norm_filter(const RawInput& in, const float* dmean, const float* den, int n_angles,
-                              int n_rows, int n_det, const FilterTables& ft, tp_dtype out_dt, void* out,
+                              int n_rows, int n_det, const FilterTables& ft, tp_dtype out_dt, int wide, void* out,
                               hipStream_t st) {
     switch (out_dt) {
-        case TP_F32: return launch_norm_filter_t<kStF32>(in, dmean, den, n_angles, n_rows, n_det, ft, out, st);
-        case TP_F16: return launch_norm_filter_t<kStF16>(in, dmean, den, n_angles, n_rows, n_det, ft, out, st);
+        case TP_F32: return launch_norm_filter_t<kStF32>(in, dmean, den, n_angles, n_rows, n_det, ft, wide, out, st);
+        case TP_F16: return launch_norm_filter_t<kStF16>(in, dmean, den, n_angles, n_rows, n_det, ft, wide, out, st);
         case TP_BF16:
-            return launch_norm_filter_t<kStBF16>(in, dmean, den, n_angles, n_rows, n_det, ft, out, st);
+            return launch_norm_filter_t<kStBF16>(in, dmean, den, n_angles, n_rows, n_det, ft, wide, out, st);
     }
     return hipErrorInvalidValue;
 }

@@ -1079,9 +1079,9 @@ tp_status tp_prepare(const tp_plan* plan, tp_filter_kind kind, tp_dtype storage)
     if (s != TP_OK) return s;
     e = tp::prepare_backproject(storage, plan->bp_k[storage], plan->bp_a[storage]);
     if (e == hipSuccess)
-        e = tp::launch_backproject_blocked(plan->geo, nullptr, storage, 0, 0.0f, nullptr, TP_F32, nullptr);
+        e = tp::launch_backproject_blocked(plan->geo, nullptr, storage, 0, 8, 0.0f, nullptr, TP_F32, nullptr);
     if (e == hipSuccess && storage == TP_F16)
-        e = tp::launch_backproject_blocked(plan->geo, nullptr, storage, 0, 0.0f, nullptr, TP_F16, nullptr);
+        e = tp::launch_backproject_blocked(plan->geo, nullptr, storage, 0, 8, 0.0f, nullptr, TP_F16, nullptr);
     if (e != hipSuccess) return hip_fail(e, "backprojection kernel attribute");
     return TP_OK;
 }
@@ -1301,7 +1301,7 @@ tp_status tp_radon(const tp_plan* plan, const float* vol, int32_t n_rows, float*
 size_t tp_fbp_workspace_bytes(const tp_plan* plan, int32_t n_rows, tp_dtype storage) {
     if (!plan || n_rows <= 0 || !valid_dtype(storage)) return 0;
     return tp_normalize_workspace_bytes(n_rows, plan->n) +
-           align256(tp::blocked_rows_bytes(n_rows, plan->na, plan->n, storage));
+           align256(tp::blocked_rows_bytes(n_rows, 8, plan->na, plan->n, storage));
 }
 
 tp_status tp_fbp_chunk(const tp_plan* plan, const uint16_t* proj, int64_t proj_stride, const uint16_t* dark,
@@ -1336,14 +1336,21 @@ tp_status tp_fbp_chunk_out(const tp_plan* plan, const uint16_t* proj, int64_t pr
     if (!vol) return fail(TP_EINVAL, "vol is null");
     if (!workspace) return fail(TP_EINVAL, "workspace is null");
     if (reinterpret_cast<uintptr_t>(workspace) & 255) return fail(TP_EINVAL, "workspace not 256-byte aligned");
-    const size_t need = tp_fbp_workspace_bytes(plan, n_rows, storage);
+    // room for n_rows rows is enough: without that for whole blocks of 8 the slices
+    // run in passes of the whole blocks that fit, or, fewer than 8, in one narrower block
+    const size_t dfb = tp_normalize_workspace_bytes(n_rows, plan->n);
+    const size_t need = dfb + align256(tp::blocked_rows_bytes(n_rows, 1, plan->na, plan->n, storage));
     if (workspace_bytes < need) return fail(TP_EINVAL, "workspace %zu < %zu bytes", workspace_bytes, need);
+    int step = n_rows, wide = 8;
+    if (workspace_bytes < tp_fbp_workspace_bytes(plan, n_rows, storage)) {
+        if (n_rows < 8) wide = n_rows;
+        else step = 8 * static_cast<int>((workspace_bytes - dfb) / tp::blocked_rows_bytes(8, 8, plan->na, plan->n, storage));
+    }
     if (tp::blocked_groups(n_rows, (plan->na + 1) / 2) > 0x7fffffffLL)
         return fail(TP_EINVAL, "n_rows=%d x n_angles=%d too large for one call", n_rows, plan->na);
     auto st = static_cast<hipStream_t>(stream);
     tp::FilterTables ft = plan->filt;
     if (kind != TP_RAMP && (s = filter_tables(plan->filt.L, kind, &ft, st)) != TP_OK) return s;
-    const size_t dfb = tp_normalize_workspace_bytes(n_rows, plan->n);
     float* dmean = static_cast<float*>(workspace);
     float* den = reinterpret_cast<float*>(static_cast<char*>(workspace) + dfb / 2);
     void* filt = static_cast<char*>(workspace) + dfb;
@@ -1357,12 +1364,19 @@ tp_status tp_fbp_chunk_out(const tp_plan* plan, const uint16_t* proj, int64_t pr
     e = tp::launch_darkflat(in, n_rows, plan->n, dmean, den, st);
     if (e != hipSuccess) return hip_fail(e, "darkflat launch");
     if ((e = mark(1)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-    e = tp::launch_norm_filter(in, dmean, den, plan->na, n_rows, plan->n, ft, storage, filt, st);
-    if (e != hipSuccess) return hip_fail(e, "norm_filter launch");
-    if ((e = mark(2)) != hipSuccess) return hip_fail(e, "hipEventRecord");
-    e = tp::launch_backproject_blocked(plan->geo, filt, storage, n_rows, static_cast<float>(M_PI / plan->na), vol,
-                                       vol_dtype, st);
-    if (e != hipSuccess) return hip_fail(e, "backproject launch");
+    const size_t slice = static_cast<size_t>(plan->N) * plan->N * dtype_size(vol_dtype);
+    for (int r0 = 0; r0 < n_rows; r0 += step) {
+        const int rows = std::min(step, n_rows - r0);
+        const int64_t roff = static_cast<int64_t>(r0) * plan->n;
+        tp::RawInput ip = in;
+        ip.proj = proj + roff;
+        e = tp::launch_norm_filter(ip, dmean + roff, den + roff, plan->na, rows, plan->n, ft, storage, wide, filt, st);
+        if (e != hipSuccess) return hip_fail(e, "norm_filter launch");
+        if (r0 == 0 && (e = mark(2)) != hipSuccess) return hip_fail(e, "hipEventRecord");
+        e = tp::launch_backproject_blocked(plan->geo, filt, storage, rows, wide, static_cast<float>(M_PI / plan->na),
+                                           static_cast<char*>(vol) + r0 * slice, vol_dtype, st);
+        if (e != hipSuccess) return hip_fail(e, "backproject launch");
+    }
     if ((e = mark(3)) != hipSuccess) return hip_fail(e, "hipEventRecord");
     return TP_OK;
 }

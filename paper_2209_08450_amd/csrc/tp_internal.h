@@ -149,9 +149,10 @@ hipError_t launch_normalize(const RawInput& in, const float* dmean, const float*
                             int n_rows, int n_det, tp_dtype out_dtype, void* sino, hipStream_t st);
 hipError_t launch_filter(const void* in, tp_dtype in_dt, void* out, tp_dtype out_dt, int64_t n_lines,
                          int n_det, const FilterTables& ft, hipStream_t st);
-// out: blocked filtered rows (blocked_rows.h) in the precision out_dt
+// out: blocked filtered rows (blocked_rows.h) in the precision out_dt, in blocks
+// of `wide` slices: 8, or all n_rows where there are fewer
 hipError_t launch_norm_filter(const RawInput& in, const float* dmean, const float* den, int n_angles,
-                              int n_rows, int n_det, const FilterTables& ft, tp_dtype out_dt, void* out,
+                              int n_rows, int n_det, const FilterTables& ft, tp_dtype out_dt, int wide, void* out,
                               hipStream_t st);
 // Work-groups of launch_norm_filter for `pieces` pieces of a slice's angles:
 // whole blocks of 8 slices, dealt to the 8 XCDs in turn.
@@ -160,9 +161,9 @@ inline int64_t blocked_groups(int n_rows, int pieces) {
     return (items + 7) / 8 * 8 * (n_rows < 8 ? n_rows : 8);
 }
 // Blocked filtered rows (blocked_rows.h): their bytes, and their backprojection.
-size_t blocked_rows_bytes(int n_rows, int na, int n, tp_dtype dt);
-hipError_t launch_backproject_blocked(const GeoTables& g, const void* rows, tp_dtype dt, int n_rows, float scale,
-                                      void* vol, tp_dtype vol_dt, hipStream_t st);
+size_t blocked_rows_bytes(int n_rows, int wide, int na, int n, tp_dtype dt);
+hipError_t launch_backproject_blocked(const GeoTables& g, const void* rows, tp_dtype dt, int n_rows, int wide,
+                                      float scale, void* vol, tp_dtype vol_dt, hipStream_t st);
 // vol: FP32 slices (vol_dt TP_F32), or FP16 slices (TP_F16, FP16 rows only)
 hipError_t launch_backproject(const GeoTables& g, const void* filt, tp_dtype dt, int n_rows, float scale,
                               void* vol, tp_dtype vol_dt, int accumulate, int slices_per_block, int angles_per_block,

@@ -51,3 +51,25 @@ def test_lprec_rows_to_sixteen(tp, na, n):
     got = tp.lprec_fbp_chunk(plan, P, D, F, workspace=_buffer(df + _up(a) + _up(b)))
     assert torch.equal(got, want)
     assert bool(torch.isfinite(want).all())
+
+
+# exactly the rows asked for: one narrower block below 8 (tiles of 16 and, at
+# N = 740, of 32), above that the whole blocks that fit and the rest behind them
+@pytest.mark.parametrize("rows", [1, 2, 5, 7, 9, 15, 37])
+@pytest.mark.parametrize("N", [60, 740])
+@pytest.mark.parametrize("storage", ["f32", "f16", "bf16"])
+def test_fbp_rows_without_whole_blocks(tp, rows, N, storage):
+    import torch
+    na, n = 13, 71
+    s, P, D, F = _scan(na, rows, n)
+    plan = tp.Plan(s.angles, n, s.center, N)
+    df, size = int(tp._normalize_ws(rows, n)), 4 if storage == "f32" else 2
+    need = df + _up(rows * na * n * size)
+    note(f"fbp workspace {rows} rows N={N} {storage}")
+    for out_dtype in ("f32", "f16") if storage == "f16" else ("f32",):
+        want = tp.fbp_chunk(plan, P, D, F, storage, out_dtype=out_dtype)
+        got = tp.fbp_chunk(plan, P, D, F, storage, workspace=_buffer(need), out_dtype=out_dtype)
+        assert torch.equal(got, want), out_dtype
+        assert bool(torch.isfinite(want.float()).all())
+    with pytest.raises(tp.TpError, match="workspace"):
+        tp.fbp_chunk(plan, P, D, F, storage, workspace=_buffer(need - 256))
