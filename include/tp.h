@@ -349,9 +349,11 @@ tp_status tp_fbp_chunk_out(const tp_plan* plan,
  * kind: filter window (tables built on first use, see tp_fourier_prepare).
  * workspace: dev, 256-byte aligned, not overlapping the inputs or vol.
  * tp_fourier_workspace_bytes(plan, n_rows) bytes process every pair of rows in
- * one pass; a smaller workspace (at least tp_fourier_workspace_bytes(plan, 2))
- * processes the rows in several passes of as many pairs as fit.  Its contents
- * are scratch.  Errors: TP_EINVAL for bad arguments (checked before any
+ * one pass; a smaller workspace processes the rows in several passes of as many
+ * pairs as fit, at least tp_fourier_workspace_bytes(plan, 2), or, slower, of one
+ * pair alone, from tp_normalize_workspace_bytes(n_rows, n_det) plus
+ * 8 max(n_angles (L + 1), 16 ceil(N / 16) M) plus 8 M^2 bytes, each rounded up
+ * to 256.  Its contents are scratch.  Errors: TP_EINVAL for bad arguments (checked before any
  * launch), TP_EUNSUPPORTED for M > 16384 or tables missing during capture.
  * ------------------------------------------------------------------------ */
 size_t tp_fourier_workspace_bytes(const tp_plan* plan, int32_t n_rows);

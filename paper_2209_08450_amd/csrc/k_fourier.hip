@@ -74,20 +74,24 @@ hipError_t fr_lds(K kernel, size_t bytes) {
 // Spectra rows: groups of four pairs of slices side by side, so that one
 // 16-byte piece holds a sample of four pairs, in two FP16 planes; entry 0 of a
 // row is zero (what the gather reads off either end), frequency k is entry
-// k + L/2 + 1.
+// k + L/2 + 1.  Without room for four pairs, one at a time: rows of one pair
+// (t.wide = 1) without the zero (t.first = 0).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t* spectra_row(uint32_t* spec, int p, int slot, const FourierTables& t) {
-    return spec + ((static_cast<int64_t>(p / kFrPairGroup) * t.na + slot) * 2 * t.SL) * kFrPairGroup + p % kFrPairGroup;
+    return spec + ((static_cast<int64_t>(p / kFrPairGroup) * t.na + slot) * 2 * t.SL) * t.wide + p % kFrPairGroup;
 }
-__device__ __forceinline__ void spectra_store(uint32_t* row, int k, int SL, float2 v) {
+// The sample of entry k (counted from frequency -L/2).
+__device__ __forceinline__ void spectra_store(uint32_t* row, int k, const FourierTables& t, float2 v) {
     uint32_t hi, lo;
     split_data(v.x, v.y, hi, lo);
-    row[static_cast<int64_t>(k) * kFrPairGroup] = hi;
-    row[(static_cast<int64_t>(SL) + k) * kFrPairGroup] = lo;
+    const int at = __mul24(k + t.first, t.wide);
+    row[at] = hi;
+    row[t.SL * t.wide + at] = lo;
 }
-__device__ __forceinline__ void spectra_zero(uint32_t* row, int SL) {
+__device__ __forceinline__ void spectra_zero(uint32_t* row, const FourierTables& t) {
+    if (t.first == 0) return;
     row[0] = 0;
-    row[static_cast<int64_t>(SL) * kFrPairGroup] = 0;
+    row[t.SL * t.wide] = 0;
 }
 // Work-group -> (pair, piece of the angles): work-groups go to the 8 XCDs in
 // turn, and the four pairs of a group run back to back on one XCD for the same
@@ -135,12 +139,12 @@ k_fr_spectra(RawInput in, int rows, const float* __restrict__ dmean, const float
     const int sl = t.slot[a];
     const bool rev = (sl & 1) != 0;
     uint32_t* row = spectra_row(spec, p, sl >> 1, t);
-    if (tid == 0) spectra_zero(row, t.SL);
+    if (tid == 0) spectra_zero(row, t);
     for (int m = tid; m < L; m += B) {
         const float2 X = buf[m];
         const int k = m < h ? m : m - L;  // m = L/2 is the -L/2 term
-        spectra_store(row, (rev ? -k : k) + h + 1, t.SL, cmul(X, t.E[k + h]));
-        if (m == h) spectra_store(row, (rev ? -h : h) + h + 1, t.SL, cmul(X, t.E[L]));  // and its +L/2 copy
+        spectra_store(row, (rev ? -k : k) + h, t, cmul(X, t.E[k + h]));
+        if (m == h) spectra_store(row, (rev ? -h : h) + h, t, cmul(X, t.E[L]));  // and its +L/2 copy
     }
 }
 
@@ -205,7 +209,9 @@ template <int NT> constexpr size_t fr_grid_lds() {
 
 // S1: one grid point per frequency sample (the weights then follow from two
 // exponentials per 8 samples); otherwise one exponential per sample.
-template <int TB, int NT, bool S1>
+// NARROW: rows of one pair.  A lane picks its sample alone and pads it with zeros
+// (the sums of the other three pairs are never stored).
+template <int TB, int NT, bool S1, bool NARROW>
 __device__ __forceinline__ void gather_tile(const FourierTables& t, const u4_t* __restrict__ spec, int4 item, int group0,
                                             int pairs, float2* __restrict__ grid, unsigned char* smem) {
     constexpr int BW = TB == 32 ? 4 : 1;                  // blocks per wave
@@ -287,6 +293,34 @@ __device__ __forceinline__ void gather_tile(const FourierTables& t, const u4_t* 
         }
     };
 
+    // The same of NARROW rows, through registers: loaded before a block is
+    // summed, written after it.
+    constexpr int kPieces = (kLoads + kFrWaves - 1) / kFrWaves;
+    uint32_t sample[NARROW ? kPieces : 1];
+    auto take = [&](int k) {
+        const int2* rows = sRow + (k & kRing) * kFrAngles;
+        const uint32_t* rows32 = reinterpret_cast<const uint32_t*>(spec);
+#pragma unroll
+        for (int s = 0; s < kPieces; ++s) {
+            const int i = s * kFrWaves + wv;
+            if (kLoads % kFrWaves != 0 && i >= kLoads) break;
+            const int part = i % kParts, pr = i / kParts % (kFrAngles / 2), pl = i / (kParts * (kFrAngles / 2));
+            const int2 row = rows[2 * pr + ((lane >> 1) & 1)];
+            const int kk = row.x + 16 * part + (lane >> 2);
+            sample[s] = 0;
+            if (static_cast<uint32_t>(kk + h) <= static_cast<uint32_t>(2 * h))
+                sample[s] = rows32[(static_cast<int64_t>(row.y) * 2 + pl) * t.SL + ((kk ^ flip) - flip) + h];
+        }
+    };
+    auto put = [&](int k) {
+#pragma unroll
+        for (int s = 0; s < kPieces; ++s) {
+            const int i = s * kFrWaves + wv;
+            if (kLoads % kFrWaves != 0 && i >= kLoads) break;
+            *reinterpret_cast<u4_t*>(smem + (k & 1) * kBuf + i * 1024 + 16 * lane) = u4_t{sample[s], 0, 0, 0};
+        }
+    };
+
     // points of the wave's blocks: operand row m = lane % 16 is point (m / 4, m % 4) of a block
     const int px = (lane >> 2) & 3, py = lane & 3, ag = lane >> 4;
     // block i of the wave starts at (bx + 16 (i / 2), by + 16 (i % 2)): any strip
@@ -302,14 +336,24 @@ __device__ __forceinline__ void gather_tile(const FourierTables& t, const u4_t* 
 
     if (wv == 0) geometry(0);
     __syncthreads();
-    if (nblk > 0) stage(0);
+    if (nblk > 0) {
+        if constexpr (NARROW) {
+            take(0);
+            put(0);
+        } else {
+            stage(0);
+        }
+    }
     wait_loads();
     __syncthreads();
     for (int k = 0; k < nblk; ++k) {
         // the geometry first: the loads into LDS that follow complete in order,
         // and nothing before the end of the block waits for them
         if (wv == 0 && k % kFrChunk == 0) geometry(k / kFrChunk + 1);
-        if (k + 1 < nblk) stage(k + 1);
+        if (k + 1 < nblk) {
+            if constexpr (NARROW) take(k + 1);
+            else stage(k + 1);
+        }
         const float4 ge = sGeo[(k & kRing) * kFrAngles + ag];
         const float cb = ge.z, sb = ge.w;
         // block 0 of the wave: its centre's offset from the ray and position on
@@ -387,6 +431,7 @@ __device__ __forceinline__ void gather_tile(const FourierTables& t, const u4_t* 
                 for (int r = 0; r < 4; ++r) acc[i][n][r] += sum[n][r];
         }
         if (kWide && k % 16 == 15) carry();
+        if (NARROW && k + 1 < nblk) put(k + 1);
         wait_loads();  // this wave's part of block k + 1 is in LDS
         __syncthreads();
     }
@@ -442,16 +487,16 @@ __device__ __forceinline__ void gather_tile(const FourierTables& t, const u4_t* 
     }
 }
 
-template <int NT, bool S1>
+template <int NT, bool S1, bool NARROW>
 __global__ void __launch_bounds__(64 * kFrWaves)
 k_fr_grid(FourierTables t, const u4_t* __restrict__ spec, int pairs, int groups, float2* __restrict__ grid) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int it = blockIdx.x / groups, group0 = (blockIdx.x - it * groups) * NT;
     const int4 item = t.items[it];
     if (it < t.n_small)
-        gather_tile<16, NT, S1>(t, spec, item, group0, pairs, grid, smem);
+        gather_tile<16, NT, S1, NARROW>(t, spec, item, group0, pairs, grid, smem);
     else
-        gather_tile<32, NT, S1>(t, spec, item, group0, pairs, grid, smem);
+        gather_tile<32, NT, S1, NARROW>(t, spec, item, group0, pairs, grid, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -580,13 +625,13 @@ k_fr_spectra_reg(RawInput in, int rows, const float* __restrict__ dmean, const f
         const int sl = t.slot[a];
         const bool rev = (sl & 1) != 0;
         uint32_t* row = spectra_row(spec, p, sl >> 1, t);
-        if (tid == 0) spectra_zero(row, t.SL);
+        if (tid == 0) spectra_zero(row, t);
 #pragma unroll
         for (int s = 0; s < kRegPts; ++s) {
             const int m = tid + B * s;
             const int k = m < h ? m : m - L;
-            spectra_store(row, (rev ? -k : k) + h + 1, t.SL, cmul(x[s], t.E[k + h]));
-            if (m == h) spectra_store(row, (rev ? -h : h) + h + 1, t.SL, cmul(x[s], t.E[L]));
+            spectra_store(row, (rev ? -k : k) + h, t, cmul(x[s], t.E[k + h]));
+            if (m == h) spectra_store(row, (rev ? -h : h) + h, t, cmul(x[s], t.E[L]));
         }
 #pragma unroll
         for (int s = 0; s < kRegPts; ++s) cur[s] = nxt[s];
@@ -670,23 +715,23 @@ k_fr_cols_reg(const float2* __restrict__ cols, const float2* __restrict__ tw, Fo
 
 size_t reg_lds(int L) { return static_cast<size_t>(L + L / 16) * sizeof(float2); }
 
-template <int NT, bool S1>
+template <int NT, bool S1, bool NARROW>
 hipError_t launch_grid_t(const FourierTables& t, const uint32_t* spec, int pairs, float2* grid, hipStream_t st) {
     constexpr size_t lds = fr_grid_lds<NT>();
     static_assert(lds <= 160 * 1024, "LDS of a CU");
-    hipError_t e = fr_lds(k_fr_grid<NT, S1>, lds);
+    hipError_t e = fr_lds(k_fr_grid<NT, S1, NARROW>, lds);
     if (e != hipSuccess) return e;
     const int groups = (pairs + kFrPairGroup * NT - 1) / (kFrPairGroup * NT);
     const dim3 g(static_cast<unsigned>(static_cast<int64_t>(t.n_items) * groups));
-    hipLaunchKernelGGL((k_fr_grid<NT, S1>), g, dim3(64 * kFrWaves), lds, st, t, reinterpret_cast<const u4_t*>(spec), pairs,
+    hipLaunchKernelGGL((k_fr_grid<NT, S1, NARROW>), g, dim3(64 * kFrWaves), lds, st, t, reinterpret_cast<const u4_t*>(spec), pairs,
                        groups, grid);
     return hipGetLastError();
 }
 
-template <int NT>
+template <int NT, bool NARROW = false>
 hipError_t launch_grid_nt(const FourierTables& t, const uint32_t* spec, int pairs, float2* grid, hipStream_t st) {
-    return t.s == 1.0f ? launch_grid_t<NT, true>(t, spec, pairs, grid, st)
-                       : launch_grid_t<NT, false>(t, spec, pairs, grid, st);
+    return t.s == 1.0f ? launch_grid_t<NT, true, NARROW>(t, spec, pairs, grid, st)
+                       : launch_grid_t<NT, false, NARROW>(t, spec, pairs, grid, st);
 }
 
 }  // namespace
@@ -722,6 +767,7 @@ hipError_t launch_fourier_spectra(const RawInput& in, int rows, const float* dme
 
 // As many pairs per work-group as there are, up to 16: they share the weights.
 hipError_t launch_fourier_grid(const FourierTables& t, const uint32_t* spec, int pairs, float2* grid, hipStream_t st) {
+    if (t.wide == 1) return launch_grid_nt<1, true>(t, spec, pairs, grid, st);
     if (pairs > 2 * kFrPairGroup) return launch_grid_nt<4>(t, spec, pairs, grid, st);
     return pairs > kFrPairGroup ? launch_grid_nt<2>(t, spec, pairs, grid, st)
                                 : launch_grid_nt<1>(t, spec, pairs, grid, st);

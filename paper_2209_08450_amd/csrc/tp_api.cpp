@@ -308,6 +308,11 @@ size_t fr_region_a(const FrDims& d, int64_t P) {
     return align256(std::max(spec, static_cast<size_t>(P) * d.cols_pair));
 }
 
+// The region for one pair alone, in rows of L + 1 samples.
+size_t fr_region_a1(const tp_plan* plan, const FrDims& d) {
+    return align256(std::max(static_cast<size_t>(plan->na) * (d.L + 1) * sizeof(float2), d.cols_pair));
+}
+
 // Workspace: dark/flat tables of every row, then (per pass of P pairs) a
 // region holding the spectra and later the column-group intermediate, then
 // the Cartesian grid.
@@ -527,6 +532,8 @@ tp_status fourier_tables(const tp_plan* plan, tp_filter_kind kind, int msp, tp::
     t.M = M;
     t.log2M = ilog2(M);
     t.SL = d.SL;
+    t.wide = tp::kFrPairGroup;
+    t.first = 1;
     t.units = units;
     t.n_items = static_cast<int>(items.size());
     t.n_small = static_cast<int>(small.size());
@@ -1471,9 +1478,11 @@ tp_status tp_fourier_fbp_chunk_out(const tp_plan* plan, const uint16_t* proj, in
     if (d.M > kFourierMaxSide) return fail(TP_EUNSUPPORTED, "Fourier grid side %d > %d", d.M, kFourierMaxSide);
     const int pairs = (n_rows + 1) / 2;
     const size_t df = tp_normalize_workspace_bytes(n_rows, plan->n);
-    if (workspace_bytes < fr_workspace(plan, n_rows, 1))
-        return fail(TP_EINVAL, "workspace %zu < %zu bytes (one pair of rows)", workspace_bytes,
-                    fr_workspace(plan, n_rows, 1));
+    // room for one pair is enough: without that for a group of four, one pair a pass
+    const size_t need = df + fr_region_a1(plan, d) + align256(d.grid_pair);
+    if (workspace_bytes < need)
+        return fail(TP_EINVAL, "workspace %zu < %zu bytes (one pair of rows)", workspace_bytes, need);
+    const bool narrow = workspace_bytes < fr_workspace(plan, n_rows, 1);
     int64_t P = static_cast<int64_t>((workspace_bytes - df) / (std::max(d.spec_pair, d.cols_pair) + d.grid_pair));
     P = std::min<int64_t>(std::max<int64_t>(P, 1), pairs);
     // work-groups of the gather per pass: at most one per 16x16 tile of half a grid and pair
@@ -1482,16 +1491,22 @@ tp_status tp_fourier_fbp_chunk_out(const tp_plan* plan, const uint16_t* proj, in
     P = std::min<int64_t>(P, 0x7fffffffLL / std::max<int64_t>({tiles, plan->na + 8, d.M}) - 3);
     while (P > 1 && fr_workspace(plan, n_rows, P) > workspace_bytes) --P;
     if (P > tp::kFrPairGroup && P < pairs) P -= P % tp::kFrPairGroup;  // whole groups of pairs in every pass
+    if (narrow) P = 1;
     if (P < 1) return fail(TP_EINVAL, "grid too large for one launch");
     auto st = static_cast<hipStream_t>(stream);
     tp::FourierTables t;
     if ((s = fourier_tables(plan, kind, msp, &t, st)) != TP_OK) return s;
+    if (narrow) {
+        t.wide = 1;
+        t.first = 0;
+        t.SL = d.L + 1;
+    }
     tp::FilterTables fm;
     if ((s = filter_tables(d.M, TP_RAMP, &fm, st)) != TP_OK) return s;
     float* dmean = static_cast<float*>(workspace);
     float* den = reinterpret_cast<float*>(static_cast<char*>(workspace) + df / 2);
     char* regA = static_cast<char*>(workspace) + df;
-    char* regB = regA + fr_region_a(d, P);
+    char* regB = regA + (narrow ? fr_region_a1(plan, d) : fr_region_a(d, P));
     uint32_t* spec = reinterpret_cast<uint32_t*>(regA);
     float2* cols = reinterpret_cast<float2*>(regA);
     float2* grid = reinterpret_cast<float2*>(regB);

@@ -74,6 +74,8 @@ struct FourierTables {
     const int4* blocks;     // first of up to four sorted angles that reach an image of the tile, their number,
                             // the image's centre (z, w: FP32 bits)
     int na, n, N, L, log2L, M, log2M, SL;  // SL = L + 2 entries per row: a zero, L + 1 samples
+    int wide, first;        // pairs side by side in spec (4), entry of frequency -L/2 (1); where there is room
+                            // for one pair only, 1 and 0: rows of one pair without the zero
     int units;              // groups of 8 samples that cover a 4x4 block's reach along a ray
     int n_items, n_small;
     float s, inv_s;         // grid points per frequency sample (M / L, a power of two >= 1)

@@ -73,3 +73,28 @@ def test_fbp_rows_without_whole_blocks(tp, rows, N, storage):
         assert bool(torch.isfinite(want.float()).all())
     with pytest.raises(tp.TpError, match="workspace"):
         tp.fbp_chunk(plan, P, D, F, storage, workspace=_buffer(need - 256))
+
+
+# spectra of one pair or two in plain rows: tiles of 32 and, from 129 angles, of
+# 16 grid points, one and two grid points per frequency sample, an odd last row,
+# rows through LDS (64 and 128 points) and in registers (1024)
+@pytest.mark.parametrize("na,rows,n,N", [(40, 1, 40, 40), (129, 5, 64, 64), (140, 4, 32, 64), (200, 3, 300, 300),
+                                         (700, 2, 64, 64)])
+@pytest.mark.parametrize("out_dtype", ["f32", "f16"])
+def test_fourier_spectra_of_one_pair(tp, na, rows, n, N, out_dtype):
+    import torch
+    s, P, D, F = _scan(na, rows, n)
+    plan = tp.Plan(s.angles, n, s.center, N)
+    L = tp.pad_len(n)
+    M = max(L, tp.pad_len(N), 64)
+    df = int(tp._normalize_ws(rows, n))
+    note(f"fourier workspace {na} x {rows} x {n}, N={N} {out_dtype}")
+    want = tp.fourier_fbp_chunk(plan, P, D, F, out_dtype=out_dtype)
+    assert bool(torch.isfinite(want.float()).all())
+    for pairs in (1, 2):
+        need = df + _up(pairs * max(8 * na * (L + 1), 8 * _up(N, 16) * M)) + _up(pairs * 8 * M * M)
+        got = tp.fourier_fbp_chunk(plan, P, D, F, workspace=_buffer(need), out_dtype=out_dtype)
+        assert torch.equal(got, want), pairs
+        if pairs == 1:
+            with pytest.raises(tp.TpError, match="workspace"):
+                tp.fourier_fbp_chunk(plan, P, D, F, workspace=_buffer(need - 256), out_dtype=out_dtype)
