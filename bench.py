@@ -237,10 +237,15 @@ def measure_peaks(log, copy_bytes: int = 2 << 30, fma_blocks: int = 4096, fma_it
 
 
 def kernel_source_hash() -> str:
-    p = os.path.join(ROOT, "paper_2209_08450_amd", "csrc", "k_backproject_blocked.hip")
-    if not os.path.exists(p):
-        return ""
-    return hashlib.sha256(open(p, "rb").read()).hexdigest()[:16]
+    """Of the fused chunk's backprojection kernel and the headers that hold its
+    row layout and its loads, LDS reads and products."""
+    h = hashlib.sha256()
+    for name in ("k_backproject_blocked.hip", "blocked_rows.h", "mfma_lds.h"):
+        p = os.path.join(ROOT, "paper_2209_08450_amd", "csrc", name)
+        if not os.path.exists(p):
+            return ""
+        h.update(open(p, "rb").read())
+    return h.hexdigest()[:16]
 
 
 def load_lamino_traffic():
