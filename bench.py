@@ -67,7 +67,7 @@ def parse():
     ap.add_argument("--precision-points", type=int, default=2048, help="sampled voxels per precision slice")
     ap.add_argument("--filter", default="ramp", choices=("ramp", "shepp", "parzen"),
                     help="filter window (the paper's tool defaults to parzen; the headline workload is ramp)")
-    ap.add_argument("--tuning", default="", help="backprojection tuning K,A (default: plan default)")
+    ap.add_argument("--tuning", default="", help="tiling K,A of tp_backproject set on the plan (the timed chunks pick their own tiles)")
     ap.add_argument("--parity-rows", type=int, default=2, help="full slices checked against the oracle")
     ap.add_argument("--cpu-seconds", type=float, default=12.0,
                     help="CPU-baseline budget: oracle slices are added until this much time is spent (0: skip)")
@@ -342,7 +342,6 @@ def main():
         k, a = (int(v) for v in args.tuning.split(","))
         for st in storages:
             plan.set_tuning(st, k, a)
-    tuning = {st: list(plan.get_tuning(st)) for st in storages}
     vol = torch.empty((rows, n, n), dtype=torch.float32, device=dev)
     ws = torch.empty(max(plan.fbp_workspace_bytes(chunk, s) for s in storages), dtype=torch.uint8, device=dev)
     chunks = [(z0, min(rows, z0 + chunk)) for z0 in range(0, rows, chunk)]
@@ -523,7 +522,7 @@ def main():
         "config": {"workload": f"fbp {n}x{n}x{rows} volume from {na} angles x {rows} rows x {n} cols "
                                f"12-bit ellipsoid scan, {FILTER_NAMES[args.filter]}, linear-interpolation "
                                f"backprojection",
-                   "storage": head, "chunk_rows": chunk, "bp_tuning": tuning},
+                   "storage": head, "chunk_rows": chunk},
         "s_per_volume": {st: round(results[st]["s_per_volume"], 4) for st in storages},
         "gups": {st: round(results[st]["gups"], 2) for st in storages},
         "rel_l2_vs_fp64_oracle": rel,
@@ -1069,7 +1068,7 @@ def main_single_launch(args):
     b.copy_(a)  # 1 GiB read + 1 GiB written
     torch.cuda.synchronize()
     print(json.dumps({"single_launch": {"storage": st, "rows": rows, "n": n, "angles": na,
-                                        "tuning": list(plan.get_tuning(st)), "copy_bytes": 1 << 30}}), flush=True)
+                                        "copy_bytes": 1 << 30}}), flush=True)
     plan.close()
 
 
@@ -1108,20 +1107,19 @@ def cfg5_check_rows(chunks, rows: int, n_even: int = 10):
 def pipeline_run(dev, n, na, rows, st, pattern, method, kind, io_dir, log, points=256, out_dtype="f32", buffers=3):
     """Host-pinned to host-pinned reconstruction through the three-stream
     pipeline (copy-in, compute, copy-out) over uneven chunks, with per-chunk
-    graphs and the autotuned backprojection tiling; the same chunks are also
-    timed with inputs resident on the device to show how much of the copy
-    time the overlap hides.  Checked against the FP64 oracle at ``points``
-    voxels of each check slice, and bitwise against the resident computation
-    on the check slices of the first three chunks.  ``out_dtype`` 'f16': FP16
-    slices (the 16-bit mode's output; half the copy-out and write bytes).
-    Returns the record."""
+    graphs; the same chunks are also timed with inputs resident on the device
+    to show how much of the copy time the overlap hides.  Checked against the
+    FP64 oracle at ``points`` voxels of each check slice, and bitwise against
+    the resident computation on the check slices of the first three chunks.
+    ``out_dtype`` 'f16': FP16 slices (the 16-bit mode's output; half the
+    copy-out and write bytes).  Returns the record."""
     import concurrent.futures as cf
 
     import numpy as np
     import torch
 
     import oracle
-    from paper_2209_08450_amd import pipeline, synth, tp, tune
+    from paper_2209_08450_amd import pipeline, synth, tp
 
     center = n / 2.0
     log(f"pipeline: generating {na} x {rows} x {n} scan on the GPU")
@@ -1132,13 +1130,10 @@ def pipeline_run(dev, n, na, rows, st, pattern, method, kind, io_dir, log, point
     lprec = method == "lprec"
     if fourier:
         plan.fourier_prepare(kind, 0)
-        k = a = None
     elif lprec:
         plan.lprec_prepare(kind)
-        k = a = None
     else:
-        k, a = tune.tune_backproject(plan, st, rows=16, use_cache=False)
-        log(f"autotuned backprojection ({st}): slices {k}, angles {a}")
+        plan.prepare(kind, st)
     chunks = pipeline.uneven_chunks(rows, pattern)
     updates = float(n) * n * na * rows
     check_z = cfg5_check_rows(chunks, rows)
@@ -1288,7 +1283,7 @@ def pipeline_run(dev, n, na, rows, st, pattern, method, kind, io_dir, log, point
                                   "log-polar backprojection" if lprec else "linear-interpolation backprojection"),
                    "storage": None if (fourier or lprec) else st, "slices_out": out_dtype,
                    "chunks": list(pattern), "n_chunks": len(chunks), "buffers": buffers,
-                   "graphs": stats.graphs_captured, "bp_tuning": None if (fourier or lprec) else [k, a]},
+                   "graphs": stats.graphs_captured},
         "s_host_to_host" if not io else "s_file_to_file": round(stats.seconds, 3),
         "s_compute_only_resident": round(t_compute, 3),
         "compute_over_host_to_host": round(t_compute / stats.seconds, 3),
