@@ -1271,7 +1271,7 @@ tp_status tp_backproject(const tp_plan* plan, const void* filt, tp_dtype in_dtyp
     const int K = plan->bp_k[in_dtype], A = plan->bp_a[in_dtype];
     if ((n_rows + K - 1) / K > 65535)
         return fail(TP_EINVAL, "n_rows=%d too large for slices_per_block=%d", n_rows, K);
-    hipError_t e = tp::launch_backproject(plan->geo, filt, in_dtype, n_rows, scale, vol, TP_F32, accumulate, K, A,
+    hipError_t e = tp::launch_backproject(plan->geo, filt, in_dtype, n_rows, scale, vol, accumulate, K, A,
                                           static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "backproject launch");
     return TP_OK;

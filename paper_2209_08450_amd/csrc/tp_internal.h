@@ -166,9 +166,8 @@ inline int64_t blocked_groups(int n_rows, int pieces) {
 size_t blocked_rows_bytes(int n_rows, int wide, int na, int n, tp_dtype dt);
 hipError_t launch_backproject_blocked(const GeoTables& g, const void* rows, tp_dtype dt, int n_rows, int wide,
                                       float scale, void* vol, tp_dtype vol_dt, hipStream_t st);
-// vol: FP32 slices (vol_dt TP_F32), or FP16 slices (TP_F16, FP16 rows only)
 hipError_t launch_backproject(const GeoTables& g, const void* filt, tp_dtype dt, int n_rows, float scale,
-                              void* vol, tp_dtype vol_dt, int accumulate, int slices_per_block, int angles_per_block,
+                              float* vol, int accumulate, int slices_per_block, int angles_per_block,
                               hipStream_t st);
 size_t backproject_lds_bytes(tp_dtype dt, int slices_per_block, int angles_per_block);
 // Sets the dynamic-LDS limit of one backprojection kernel instance (no launch).
