@@ -345,7 +345,8 @@ k_backproject_blocked(GeoTables g, const uint16_t* __restrict__ rows, int n_rows
                     if constexpr (PB == 2) low[i][t] = mfma16(wt[0], o.q[t][1], low[i][t]);
                 }
             };
-            // the reads of block i + 1 are in flight during the products of block i
+            // (unrolled: the compiler moves reads of later blocks ahead of products as
+            // far as registers allow)
 #pragma unroll
             for (int i = 0; i < BW; ++i) {
                 Block cur;

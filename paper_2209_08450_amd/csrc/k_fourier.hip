@@ -378,9 +378,12 @@ __device__ __forceinline__ void gather_tile(const FourierTables& t, const u4_t* 
             auto unit = [&](auto first, float q, uint32_t src) {
                 float w[8];
                 if constexpr (S1) {
-                    // the recurrence starts anew every 8 samples: a start that
-                    // underflows (14 or more grid points away) has no weight
-                    // above 2^-30 in its 8 samples
+                    // the recurrence starts anew every 8 samples.  kappa is 3.2 /
+                    // half_width: a start underflows from 6.26 sqrt(half_width) grid
+                    // points away, so its samples, at most 7 nearer, weigh at most
+                    // 2^-15.9 at half_width 3, 2^-24.5 at 4 and 2^-31 above, all
+                    // beyond the radius (that setting's own error is 2^-9.5, 2^-12.7,
+                    // 2^-15.9 and less)
                     float v = __builtin_amdgcn_exp2f(__builtin_fmaf(-kap * q, q, e0));
                     float ratio = __builtin_amdgcn_exp2f(__builtin_fmaf(kap2, q, -kap));
 #pragma unroll

@@ -178,7 +178,7 @@ hipError_t launch_radon(const GeoTables& g, const float* vol, int n_rows, float*
 
 hipError_t launch_fourier_spectra(const RawInput& in, int rows, const float* dmean, const float* rden,
                                   const float2* tw_L, const FourierTables& t, uint32_t* spec, hipStream_t st);
-// Most samples of a spectra row for one pair of slices: pairs are stored in fours.
+// Pairs of slices side by side in a group of the spectra: one 16-byte piece.
 constexpr int kFrPairGroup = 4;
 hipError_t launch_fourier_grid(const FourierTables& t, const uint32_t* spec, int pairs, float2* grid, hipStream_t st);
 hipError_t launch_fourier_rows(const FourierTables& t, const float2* tw_M, const float2* grid, int pairs,
