@@ -273,8 +273,14 @@ tp_status tp_radon(const tp_plan* plan, const float* vol, int32_t n_rows, float*
  *   vol = (pi / n_angles) R^T ( H * normalize(proj, dark, flat) )
  * The -log sinogram never leaves the chip: the filter kernel normalises raw
  * counts in registers, filters in FP32 and stores only the filtered rows, in
- * `storage` precision and in whole blocks of 8 slices, into the workspace.  Inputs as for tp_normalize
- * (n_angles, n_det from the plan); vol: dev float [n_rows][N][N] (overwritten).
+ * whole blocks of 8 slices, into the workspace.  Rows by `storage`: TP_F32 two
+ * FP16 values per sample (22 bits and a sign), TP_F16 and TP_BF16 the rounded
+ * sample.  The sums over angles are FP32, from products of 16-bit operands:
+ * TP_F32 rows meet weights of two FP16 values (three products; the fourth, below
+ * 2^-22 of its term, is left out), TP_BF16 rows the same weights, TP_F16 rows
+ * weights rounded to FP16.  With TP_F32 the error against FP64 measures at or
+ * below that of FP32 rows, weights and products.  Inputs as for tp_normalize (n_angles,
+ * n_det from the plan); vol: dev float [n_rows][N][N] (overwritten).
  * kind: filter window at the plan's pad length 2^ceil(log2(2 n_det)); windows
  * other than TP_RAMP build their tables on first use (tp_filter_prepare first
  * when the call will be graph-captured; else TP_EUNSUPPORTED during capture).
@@ -342,7 +348,9 @@ tp_status tp_fbp_chunk_out(const tp_plan* plan,
  * division by the Gaussian's transform undoes the resampling kernel
  * (unequally spaced FFT with oversampling >= 2).  half_width is the Gaussian's
  * truncation radius in grid points (0 selects 6; 3..8 allowed): relative error
- * about exp(-2.2 half_width) of the exact sum, plus FP32 rounding.
+ * about exp(-2.2 half_width) of the exact sum, plus rounding: spectra and weights
+ * meet as two FP16 values each (three products, FP32 sums), at or below the error
+ * of FP32 ones.
  *
  * Inputs as for tp_fbp_chunk (raw counts, strides, dark/flat frames; n_angles,
  * n_det from the plan); vol: dev float [n_rows][N][N] (overwritten);

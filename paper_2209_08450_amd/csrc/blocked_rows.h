@@ -17,7 +17,8 @@ namespace {
 
 enum { kStF16 = 0, kStBF16 = 1, kStF32 = 2 };
 
-// Per storage type: row planes, weight planes, angles per staged block.
+// Per storage type: row planes, weight planes, angles per staged block (FP32 rows
+// at 4: 16 slices of 256 x 256 from 180 angles 0.060 ms, at 8 0.053).
 template <int ST> struct Blocked;
 template <> struct Blocked<kStF16> { static constexpr int PB = 1, PA = 1, A = 8; };
 template <> struct Blocked<kStBF16> { static constexpr int PB = 1, PA = 2, A = 8; };

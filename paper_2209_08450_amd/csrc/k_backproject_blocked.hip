@@ -46,12 +46,14 @@
 // 4-byte address, which ran at a fraction of the LDS rate: 69 ms where the
 // transposing reads take 21.)
 //
-// What bounds it, FP16 rows, 128 slices of the 2048-cubed scan, 21 ms: vector
-// instructions (18 per weights and 4 per staged KiB, 3.5e3 of 6.2e3 cycles per
-// block of angles and CU), LDS reads (2.9e3; 1 byte per voxel, slice and angle
-// plus the table), matrix instructions (2.0e3).  It replaced a kernel with one
-// dot product per voxel, slice and angle (57 ms); FP32 rows (32 slices) 21.4 ->
-// 13.7 ms, BF16 (37 ragged) 8.9 -> 4.3 ms.
+// What bounds it (counters of 256 slices of the 2048-cubed scan; a CU issues one
+// vector instruction a cycle at the half rate of conversions, permutes and
+// comparisons, two at the full one): FP16 rows 45.4 ms (a kernel with one dot
+// product per voxel, slice and angle: 115.6), per 4x4 block, 4 angles and 64
+// slices 20.8 vector instructions (0.48 a cycle and CU), 9.9 LDS reads (the LDS
+// busy 0.52 of the time) and 4 matrix instructions (0.37), in turn; BF16 rows 62.5
+// ms (150.9); FP32 rows 122 ms (162.6), per 32 slices 37.8 vector instructions
+// (0.65), 9.9 LDS reads (0.38) and 6 matrix instructions (0.41).
 #include <type_traits>
 
 #include "blocked_rows.h"

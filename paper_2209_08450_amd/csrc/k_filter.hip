@@ -175,7 +175,7 @@ k_filter_reg(const TI* in, TO* out, int64_t n_lines, int n, int off, FilterTable
 // hold no registers.  Otherwise the same tests run on the runtime offsets
 // (each is uniform over the work-group).
 // 4096 points: held to 168 registers, three work-groups of 4 waves to a CU (170
-// and two: 2.13 ms for 128 rows of 2048 angles x 2048 columns, three 1.86; the
+// and two: 2.13 ms for 128 rows of 2048 angles x 2048 columns, three 1.71; the
 // other lengths fit as they are).
 template <int L, int ST, bool HALF>
 __global__ void __launch_bounds__(L / kRegPts, L == 4096 ? 3 : 1)

@@ -355,7 +355,8 @@ k_lp_ktable(LprecTables t, float2* __restrict__ kt) {
 // whole 128-byte lines for the transform over eta that reads them next cost
 // this kernel more than that one gains, and fewer lines the other way round.
 //
-// Bound: vector work (60% of the time), then the exchanges' barriers.  24
+// Bound: vector work (0.83 instructions a cycle and CU of one to two there can
+// be), then the exchanges' barriers (waves wait a third of their cycles).  24
 // columns of 8192 eta, 2048 -> 16384 points: 24.5 ms as one transform of 16384
 // points per column, 6.8 ms so (tried at 8.3, before the twiddles lay in the
 // order of their use: 512 threads for 4 eta 12.3, twiddles in registers 9.0, the
@@ -456,8 +457,8 @@ k_lp_conv_tab(const float2* __restrict__ ghat, LprecTables t, int pairs, float2*
 // ---------------------------------------------------------------------------
 // Inverse transform over sigma: one work-group per (pair, span, row); the
 // four rows that share their lines run back to back on one XCD.  Output F
-// [pair][span][row][nj] (the rho window).  Bound: memory (7.4 GB read, 2.7
-// written for 24 x 4720 rows of 8192 points: 3.8 ms; two rows of a group of 16
+// [pair][span][row][nj] (the rho window).  Bound: memory (7.4 GB read, 5.7
+// written for 24 x 4707 rows of 8192 points: 3.6 ms; two rows of a group of 16
 // per work-group, 184 registers and one work-group to a CU: 7.8 ms).
 // ---------------------------------------------------------------------------
 template <int NS>

@@ -234,7 +234,7 @@ class Plan:
         return self._h
 
     def set_tuning(self, storage, slices_per_block: int, angles_per_block: int):
-        """Backprojection (slices per block, angles per block) for one storage type."""
+        """tp_backproject's (slices per block, angles per block) for one storage type; fbp_chunk picks its own tiles."""
         _check(_plan_set_tuning(self._h, dtype_code(storage), int(slices_per_block), int(angles_per_block)))
 
     def get_tuning(self, storage):
