@@ -73,12 +73,14 @@ __device__ __forceinline__ f4_t mfma16(u4_t a, u4_t b, f4_t c) {
                                                   0, 0);
 }
 
-// x and y rounded to FP16, and what that misses, each as a pair.
+// x and y rounded to FP16, and what that misses (exact before it is rounded),
+// each as a pair.  The differences are one mixed-precision FMA each, written out:
+// from C they become a conversion and a subtraction.
 __device__ __forceinline__ void split_pair(float x, float y, uint32_t& hi, uint32_t& lo) {
-    const half2_t h = __builtin_convertvector((f2_t{x, y}), half2_t);
-    // (one mixed-precision FMA each)
-    const f2_t r{__builtin_fmaf(static_cast<float>(h.x), -1.0f, x), __builtin_fmaf(static_cast<float>(h.y), -1.0f, y)};
-    hi = __builtin_bit_cast(uint32_t, h);
+    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2_t{x, y}), half2_t));
+    f2_t r;
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r.x) : "v"(hi), "v"(x));
+    asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r.y) : "v"(hi), "v"(y));
     lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, half2_t));
 }
 
