@@ -48,12 +48,12 @@
 //
 // What bounds it (counters of 256 slices of the 2048-cubed scan; a CU issues one
 // vector instruction a cycle at the half rate of conversions, permutes and
-// comparisons, two at the full one): FP16 rows 45.4 ms (a kernel with one dot
+// comparisons, two at the full one): FP16 rows 44.7 ms (a kernel with one dot
 // product per voxel, slice and angle: 115.6), per 4x4 block, 4 angles and 64
 // slices 20.8 vector instructions (0.48 a cycle and CU), 9.9 LDS reads (the LDS
-// busy 0.52 of the time) and 4 matrix instructions (0.37), in turn; BF16 rows 62.5
-// ms (150.9); FP32 rows 122 ms (162.6), per 32 slices 37.8 vector instructions
-// (0.65), 9.9 LDS reads (0.38) and 6 matrix instructions (0.41).
+// busy 0.52 of the time) and 4 matrix instructions (0.37), in turn; BF16 rows 58.7
+// ms (150.9); FP32 rows 114 ms (162.6), per 32 slices 35.8 vector instructions
+// (0.63), 9.9 LDS reads (0.39) and 6 matrix instructions (0.42).
 #include <type_traits>
 
 #include "blocked_rows.h"

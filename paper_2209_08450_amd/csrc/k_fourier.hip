@@ -185,12 +185,12 @@ k_fr_spectra(RawInput in, int rows, const float* __restrict__ dmean, const float
 // (integer + FP32 fraction), lanes add only their in-tile offsets, so the
 // coordinates keep FP32 precision at any grid size.
 //
-// Bound: vector work on the weights and their split (7.6 vector instructions per
+// Bound: vector work on the weights and their split (7.5 vector instructions per
 // matrix product in all, 0.41 a cycle and CU, the matrix cores busy 0.22 of the
 // time); waves wait half of their cycles, 16 of them taking a tile's blocks of
 // angles (8 at 2048 angles) in step, each waiting for the busiest.  2048 angles, 32
 // pairs, 4096^2 grid: 9.5 ms as a gather per grid point and pair, 3.4 ms so; 721
-// angles, 5 pairs, 2048^2: 0.57 -> 0.31 ms, the longest chain of blocks around the
+// angles, 5 pairs, 2048^2: 0.57 -> 0.29 ms, the longest chain of blocks around the
 // origin.  Tried and not better: wave priorities, all LDS reads of a product group
 // ahead of its weights.
 // ---------------------------------------------------------------------------
