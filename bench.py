@@ -136,8 +136,8 @@ def filter_roofline(storage: str, ms_per_volume: float, n_angles: int, rows: int
             "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(gbs / PEAK_HBM_GBS, 4) if gbs else None,
             "frac_of_measured_copy": round(gbs / measured_copy_gbs, 4) if gbs and measured_copy_gbs else None,
             "bytes_per_volume": nbytes, "ms_per_volume": round(ms_per_volume, 2),
-            "note": "moves exactly its algorithmic bytes (FETCH_SIZE / WRITE_SIZE); its time is the FFT arithmetic "
-                    "in registers and LDS, about 4 % of a volume's time"}
+            "note": "moves its algorithmic bytes within a tenth (FETCH_SIZE / WRITE_SIZE); its time is the FFT arithmetic "
+                    "in registers and LDS, 4 to 8 % of a volume's time"}
 
 
 def host_cpu_model() -> str:
