@@ -186,10 +186,10 @@ k_fr_spectra(RawInput in, int rows, const float* __restrict__ dmean, const float
 // coordinates keep FP32 precision at any grid size.
 //
 // Bound: vector work on the weights and their split (7.5 vector instructions per
-// matrix product in all, 0.41 a cycle and CU, the matrix cores busy 0.22 of the
+// matrix product in all, 0.42 a cycle and CU, the matrix cores busy 0.23 of the
 // time); waves wait half of their cycles, 16 of them taking a tile's blocks of
 // angles (8 at 2048 angles) in step, each waiting for the busiest.  2048 angles, 32
-// pairs, 4096^2 grid: 9.5 ms as a gather per grid point and pair, 3.4 ms so; 721
+// pairs, 4096^2 grid: 9.5 ms as a gather per grid point and pair, 3.3 ms so; 721
 // angles, 5 pairs, 2048^2: 0.57 -> 0.29 ms, the longest chain of blocks around the
 // origin.  Tried and not better: wave priorities, all LDS reads of a product group
 // ahead of its weights.
@@ -400,26 +400,23 @@ __device__ __forceinline__ void gather_tile(const FourierTables& t, const u4_t* 
                         w[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(-kap * qj, qj, e0));
                     }
                 }
-                u4_t hi, lo;
+                u4_t hi, lo, hiy;  // hiy: the first values for the samples' second ones
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     uint32_t a, b;
                     split_pair(w[2 * j], w[2 * j + 1], a, b);
                     hi[j] = a;
                     lo[j] = b;
+                    hiy[j] = low_weights(a);
                 }
 #pragma unroll
                 for (int n = 0; n < NT; ++n) {
-                    const u4_t x = read_slots(src + n * kTile);
+                    const u4_t x = read_slots(src + n * kTile), y = read_slots(src + n * kTile + kPlane);
                     if constexpr (first.value) sum[n] = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
-                    sum[n] = mfma16(lo, x, sum[n]);  // the smaller product first
+                    sum[n] = mfma16(lo, x, sum[n]);  // smallest products first
+                    sum[n] = mfma16(hiy, y, sum[n]);
                     sum[n] = mfma16(hi, x, sum[n]);
                 }
-                // (after the others: the weights take the place of the first ones)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) hi[j] = low_weights(hi[j]);
-#pragma unroll
-                for (int n = 0; n < NT; ++n) sum[n] = mfma16(hi, read_slots(src + n * kTile + kPlane), sum[n]);
             };
             unit(std::true_type{}, q0, rowp);
             float q = q0;
